@@ -306,10 +306,13 @@ def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool) -> str:
     kernel for bf16/fp16 tensors in untiled 64-lane chunks when the chunks
     exceed the general kernel's resident waves (24 a compute unit: the LDS of
     three 8-wave workgroups) but fit the 16-wave kernel's (32 a compute unit),
-    the general kernel otherwise.  The library takes the same decision from the
+    its kernel for few chunks (up to eight 64-lane chunks a compute unit), the
+    general kernel otherwise.  The library takes the same decision from the
     runtime's occupancy figures."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if lanes == 64 and n_chunks <= 8 * cus:
+        return "wc_decode_small_kernel"
     if (all(d in ("bf16", "fp16") for d in dtypes) and lanes == 64 and not tiled
             and 24 * cus < n_chunks <= 32 * cus):
         return "wc_decode_wide_kernel"

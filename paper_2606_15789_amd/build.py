@@ -14,6 +14,7 @@ SOURCES = [os.path.join(CSRC, "wc_host.cpp"), os.path.join(CSRC, "wc_decode.hip"
            os.path.join(CSRC, "wc_gemm_wide.hip"), os.path.join(CSRC, "wc_gemm_wide_bf16.hip"),
            os.path.join(CSRC, "wc_encode.hip"), os.path.join(CSRC, "wc_stream.hip")]
 HEADERS = [os.path.join(CSRC, "wc_internal.h"), os.path.join(CSRC, "wc_decoder.h"),
+           os.path.join(CSRC, "wc_ring.h"),
            os.path.join(os.path.dirname(HERE), "include", "wc.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("WC_OFFLOAD_ARCH", "gfx950")

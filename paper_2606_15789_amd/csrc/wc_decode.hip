@@ -1,7 +1,8 @@
 // wc_decode.hip -- wc_decode: one launch decodes every chunk of a blob's
 // tensors into the caller's buffers (Alg. 2; the decoder is in wc_decoder.h).
-// The general kernel is here; bf16/fp16 launches that just overflow its
-// resident waves run on the 16-wave kernel of wc_decode_wide.hip.
+// The general kernel and the one for few chunks are here; bf16/fp16 launches
+// that just overflow the general kernel's resident waves run on the 16-wave
+// kernel of wc_decode_wide.hip.
 
 #include <mutex>
 #include <utility>
@@ -11,34 +12,30 @@
 
 namespace {
 
-__global__ __launch_bounds__(kThreads) void wc_decode_kernel(LaunchArgs a) {
+// Chunks to a workgroup of the small kernel, at most and in smaller launches.
+// Up to four to a compute unit, workgroups of four have a SIMD for each decoding
+// wave (128 chunks: 42 us, against 45 in workgroups of eight).
+constexpr int kSmallChunks = 8, kFewChunks = 4;
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6)))
+void wc_decode_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-
   const uint32_t wg = xcd_order(blockIdx.x, gridDim.x);
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  // the wave index is uniform across the wave; say so, so chunk metadata and
-  // buffer descriptors live in scalar registers
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t per_wave = T.lanes == 32 ? 2u : 1u;
-  const uint32_t chunk0 = ((wg - T.wg0) * kWaves + wave) * per_wave;
-  const IndexPre pre = load_index(a, T, chunk0, per_wave);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk0 >= T.n_chunks) return;
+  const DevTensor T = tensor_of<false>(a, wg);  // its registers have no room for all fields
+  const WaveOf w = wave_of(a, T, wg, kWaves, T.lanes == 32 ? 2u : 1u);
+  auto build = [&] {
+    build_table(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  };
   // instantiate one decoder per (format, lanes, tiling)
   auto run = [&](auto gc, auto lc) {
     constexpr int G = decltype(gc)::value, L = decltype(lc)::value;
     if (T.tiled)
-      decode_chunks<G, L, true>(a, T, chunk0, lane, tab, ring[wave], pre);
+      decode_chunks<G, L, true>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, build);
     else
-      decode_chunks<G, L, false>(a, T, chunk0, lane, tab, ring[wave], pre);
+      decode_chunks<G, L, false>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, build);
   };
   auto by_kind = [&](auto lc) {
     switch (T.kind) {
@@ -53,27 +50,84 @@ __global__ __launch_bounds__(kThreads) void wc_decode_kernel(LaunchArgs a) {
     by_kind(std::integral_constant<int, 64>{});
 }
 
+// Launches of few 64-lane chunks: waves 0 .. kChunks - 1 decode a chunk each in
+// steps of one LDS round trip, fed by the others (wc_ring.h).  Bound by the
+// chain of a chunk's steps.  Rings of 1024 entries leave LDS for one workgroup of
+// eight chunks, or two of four, to a compute unit: eight chunks, which is where
+// the kernel ends, since with more the general kernel's 24 waves win (8B int8,
+// 3332 chunks of 1024 steps: 135 us there, 168 to 185 us here).  On a 4 MB
+// bf16 projection (128 chunks of 512 steps) a launch takes 39 us against 56 on
+// the general kernel, on the 8B int4 layer (1760 of 2048 steps) 132 against
+// 184, on 16 ragged fp8 tensors (1340 of 512 steps) 48 against 57.
+template <int kChunks>
+__global__ __launch_bounds__(kChunks * 128) void wc_decode_small_kernel(LaunchArgs a) {
+  // the table at LDS address 0 (a slot times 8 is its entry's address), then the
+  // rings; the prefix sums the table is built from lie in the first ring, which
+  // is filled after the build
+  constexpr uint32_t kRings = 8u * wc::kTableSize;
+  static_assert(260 * 4 <= kRingWritten, "the prefix sums fit the first ring");
+  __shared__ __align__(16) uint8_t smem[kRings + kChunks * kRingWaveBytes];
+  const uint32_t wg = xcd_order(blockIdx.x, gridDim.x);
+  const DevTensor T = tensor_of(a, wg);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = __lane_id();
+  const bool feeder = wave >= kChunks;
+  const uint32_t slot = feeder ? wave - kChunks : wave;
+  const uint32_t chunk = (wg - T.wg0) * kChunks + slot;
+  const IndexPre pre = load_index(a, T, chunk, 1u);
+  uint2* tab = reinterpret_cast<uint2*>(smem);
+  uint32_t* ring = reinterpret_cast<uint32_t*>(smem + kRings + slot * kRingWaveBytes);
+  auto build = [&] {
+    build_table<kChunks * 128>(a, T, tab, reinterpret_cast<uint32_t*>(smem + kRings),
+                                    threadIdx.x);
+    __syncthreads();
+  };
+  if (feeder) {
+    const uint32_t group = T.kind == kSplit16 ? 8u : (T.kind == kByte ? 16u : 32u);
+    const Chain<64> c =
+        open_chain<64, true>(a, T, min(chunk, T.n_chunks - 1u), group, lane, ring, pre);
+    feed(c.rs, c.wbase[0], __builtin_amdgcn_readfirstlane(lds_address(ring)), lane, build);
+    return;
+  }
+  auto run = [&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    if (T.tiled)
+      decode_chunks<G, 64, true, 0, 0, 16, false, 0, true>(a, T, chunk, lane, tab, ring, pre,
+                                                           build);
+    else
+      decode_chunks<G, 64, false, 0, 0, 16, false, 0, true>(a, T, chunk, lane, tab, ring, pre,
+                                                            build);
+  };
+  switch (T.kind) {
+    case kSplit16: run(std::integral_constant<int, 2>{}); break;
+    case kByte: run(std::integral_constant<int, 4>{}); break;
+    default: run(std::integral_constant<int, 8>{}); break;
+  }
+}
+
 // Waves of the general kernel and of the 16-bit wide kernel resident on the
-// current device at once, from the runtime's occupancy calculation, worked
-// out once per device ({0, 0} when unknown: the general kernel is used).
+// current device at once, from the runtime's occupancy calculation, and the most
+// chunks of the small kernel's two workgroup sizes, worked out once per device
+// (zeros when unknown: the general kernel is used).
 struct Capacity {
-  uint64_t general, wide;
+  uint64_t general, wide, small, few;
 };
 
 Capacity capacity() {
   static std::mutex mu;
   static std::vector<std::pair<int, Capacity>> known;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return Capacity{0, 0};
+  if (hipGetDevice(&dev) != hipSuccess) return Capacity{0, 0, 0, 0};
   std::lock_guard<std::mutex> lock(mu);
   for (const auto& k : known)
     if (k.first == dev) return k.second;
-  Capacity c{0, 0};
+  Capacity c{0, 0, 0, 0};
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
       hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &per_cu, reinterpret_cast<const void*>(wc_decode_kernel), kThreads, 0) == hipSuccess)
-    c = Capacity{uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves), wc::wide_resident_waves()};
+    c = Capacity{uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves), wc::wide_resident_waves(),
+                 uint64_t(cus) * kSmallChunks, uint64_t(cus) * kFewChunks};
   known.push_back({dev, c});
   return c;
 }
@@ -107,22 +161,29 @@ extern "C" wc_status wc_decode(const wc_blob* desc, const void* dev_blob, void* 
     // the tensors of one launch: the next kMaxLaunchTensors that have chunks
     uint32_t end = t, nt = 0;
     uint64_t chunks = 0;
-    bool wide_fits = true;
+    bool wide_fits = true, lanes64 = true;
     for (; end < n && nt < kMaxLaunchTensors; end++) {
       const wc::TensorInfo& T = P.tensors[end];
       if (T.n_chunks == 0) continue;
       nt++;
       chunks += T.n_chunks;
+      lanes64 = lanes64 && T.lanes == 64;
       wide_fits = wide_fits && wc::has_raw(T.dtype) &&
                   T.lanes == 64 && !T.tile_r;
     }
     if (nt == 0) break;
-    bool wide = false;
-    if (wide_fits) {
+    bool wide = false, small = false, few = false;
+    if (lanes64) {
       const Capacity cap = capacity();
-      wide = cap.general && cap.wide > cap.general && chunks > cap.general && chunks <= cap.wide;
+      wide = wide_fits && cap.general && cap.wide > cap.general && chunks > cap.general &&
+             chunks <= cap.wide;
+      small = chunks <= cap.small;
+      few = chunks <= cap.few;
     }
-    const uint64_t waves = wide ? uint64_t(wc::kWideWaves) : uint64_t(kWaves);
+    const uint64_t waves = wide    ? uint64_t(wc::kWideWaves)
+                           : few   ? uint64_t(kFewChunks)
+                           : small ? uint64_t(kSmallChunks)
+                                   : uint64_t(kWaves);
     uint32_t wgs = 0;
     nt = 0;
     for (; t < end; t++) {
@@ -132,12 +193,19 @@ extern "C" wc_status wc_decode(const wc_blob* desc, const void* dev_blob, void* 
       const uint64_t per_group = waves * (T.lanes == 32 ? 2u : 1u);
       wgs += (uint32_t)((T.n_chunks + per_group - 1) / per_group);
     }
-    args.n_tensors = nt;
+    set_tensors(args, nt);
     if (wide) {
       if (!wc::wide_launch(&args, sizeof args, wgs, stream)) return WC_EHIP;
     } else {
-      hipLaunchKernelGGL(wc_decode_kernel, dim3(wgs), dim3(kThreads), 0,
-                         reinterpret_cast<hipStream_t>(stream), args);
+      const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+      if (few)
+        hipLaunchKernelGGL(wc_decode_small_kernel<kFewChunks>, dim3(wgs), dim3(kFewChunks * 128), 0,
+                           st, args);
+      else if (small)
+        hipLaunchKernelGGL(wc_decode_small_kernel<kSmallChunks>, dim3(wgs),
+                           dim3(kSmallChunks * 128), 0, st, args);
+      else
+        hipLaunchKernelGGL(wc_decode_kernel, dim3(wgs), dim3(kThreads), 0, st, args);
       if (hipGetLastError() != hipSuccess) return WC_EHIP;
     }
   }

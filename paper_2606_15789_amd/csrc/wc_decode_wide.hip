@@ -18,21 +18,13 @@ __global__ __launch_bounds__(wc::kWideWaves * 64) void wc_decode_wide_kernel(Lau
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[wc::kWideWaves][wc_ring_words() / 2];
-
   const uint32_t wg = xcd_order(blockIdx.x, gridDim.x);
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk0 = (wg - T.wg0) * wc::kWideWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk0, 1u);
-  build_table<wc::kWideWaves * 64>(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk0 >= T.n_chunks) return;
-  decode_chunks<2, 64, false>(a, T, chunk0, lane, tab, ring[wave], pre);
+  const DevTensor T = tensor_of(a, wg);
+  const WaveOf w = wave_of(a, T, wg, wc::kWideWaves, 1u);
+  decode_chunks<2, 64, false>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<wc::kWideWaves * 64>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 }  // namespace

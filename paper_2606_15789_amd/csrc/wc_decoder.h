@@ -51,6 +51,7 @@
 #include <utility>
 
 #include "wc_internal.h"
+#include "wc_ring.h"
 
 namespace {
 
@@ -110,6 +111,7 @@ struct LaunchArgs {
   uint64_t err;          // int32_t* or 0
   uint32_t n_tensors;
   uint32_t m;            // fused GEMM: rows of x (and of y) in every job
+  uint32_t wg0[kMaxLaunchTensors];  // first workgroup of each tensor; all ones past the last
   DevTensor t[kMaxLaunchTensors];
 };
 
@@ -137,12 +139,21 @@ __device__ __forceinline__ void report(const LaunchArgs& a, uint32_t bits) {
   if (a.err && bits) atomicOr(reinterpret_cast<int32_t*>(a.err), (int32_t)bits);
 }
 
-// Decode table of one tensor: slot -> {f | sym << 24, slot - cum_sym}, built
-// by a workgroup of kT threads.
+// The symbol byte of a table entry.  A 16-bit word is sign | e7..e1 in its high
+// byte and e0 | mantissa in its low byte: an exponent byte rotated right by one
+// has both parts where the word needs them, so one bit select against the raw
+// byte makes the word (assemble), with no shift.
+__device__ __forceinline__ uint32_t table_symbol(uint32_t kind, uint32_t s) {
+  return kind == kSplit16 ? (s >> 1) | ((s & 1u) << 7) : s;
+}
+
+// Decode table of one tensor: slot -> {f | table symbol << 24, slot - cum_sym},
+// built by a workgroup of kT threads.
 template <int kT = kThreads>
 __device__ void build_table(const LaunchArgs& a, const DevTensor& T, uint2* tab, uint32_t* cum,
                             uint32_t tid) {
-  const uint16_t* fr = reinterpret_cast<const uint16_t*>(a.blob + T.freq_off);
+  typedef __attribute__((address_space(1))) const uint16_t gu16;  // global: no flat access
+  gu16* fr = (gu16*)(a.blob + T.freq_off);
   if (tid < 64) {
     uint32_t f[4];
 #pragma unroll
@@ -180,8 +191,25 @@ __device__ void build_table(const LaunchArgs& a, const DevTensor& T, uint2* tab,
   for (uint32_t j = j0; j < j0 + kPer; j++) {
     while (s < 255 && cum[s + 1] <= j) s++;
     uint32_t f = cum[s + 1] - cum[s];
-    tab[j] = make_uint2(f | (s << 24), j - cum[s]);
+    tab[j] = make_uint2(f | (table_symbol(T.kind, s) << 24), j - cum[s]);
   }
+}
+
+// The first slot of a table symbol (the table holds the symbols in ascending
+// order): with it a lane's last entry gives its final state.
+__device__ __forceinline__ uint32_t first_slot(const uint2* __restrict__ tab, uint32_t kind,
+                                               uint32_t ts) {
+  auto symbol = [&](uint32_t t) {
+    return kind == kSplit16 ? ((t << 1) & 0xFFu) | (t >> 7) : t;
+  };
+  const uint32_t s = symbol(ts);
+  uint32_t lo = 0, hi = wc::kTableSize - 1;  // the entry at hi is of symbol s or above
+#pragma unroll
+  for (uint32_t k = 0; k < wc::kProbBits; k++) {
+    const uint32_t mid = (lo + hi) >> 1;
+    if (symbol(tab[mid].x >> 24) < s) lo = mid + 1; else hi = mid;
+  }
+  return lo;
 }
 
 // One decoded dword (G symbols) from the table entries' low words (symbol in
@@ -189,11 +217,12 @@ __device__ void build_table(const LaunchArgs& a, const DevTensor& T, uint2* tab,
 template <int G>
 __device__ __forceinline__ uint32_t assemble(const uint32_t (&lo)[G], uint32_t raw2) {
   if constexpr (G == 2) {
-    // word = raw bit 7 -> bit 15 | coded byte -> bits 14..7 | raw bits 6..0
-    const uint32_t E = __builtin_amdgcn_perm(lo[1], lo[0], 0x0C070C03u);  // e0 | e1 << 16
+    // word = raw bit 7 -> bit 15 | coded byte -> bits 14..7 | raw bits 6..0; the
+    // coded byte comes rotated (table_symbol): e0 in bit 7, e7..e1 below
+    const uint32_t E = __builtin_amdgcn_perm(lo[1], lo[0], 0x07070303u);  // e0 e0 e1 e1
     const uint32_t P = __builtin_amdgcn_perm(0u, raw2, 0x01010000u);       // r0 r0 r1 r1
     const uint32_t M = 0x807F807Fu;
-    return (P & M) | ((E << 7) & ~M);
+    return (P & M) | (E & ~M);
   } else if constexpr (G == 4) {
     const uint32_t b01 = __builtin_amdgcn_perm(lo[1], lo[0], 0x0C0C0703u);
     const uint32_t b23 = __builtin_amdgcn_perm(lo[3], lo[2], 0x0C0C0703u);
@@ -216,6 +245,7 @@ template <int L>
 struct Chain {
   static constexpr int kH = 64 / L;
   __amdgpu_buffer_rsrc_t rs;  // the chunks' records
+  uint32_t rec_hdr[3], len;   // the record's header words, loaded late, and its bytes
   __amdgpu_buffer_rsrc_t rr;  // the chunks' raw bytes (16-bit formats)
   __amdgpu_buffer_rsrc_t os;  // the chunks' decoded bytes
   uint32_t* ring;             // LDS word rings, one per half (kHalfRing32 u32 each)
@@ -261,8 +291,11 @@ struct IndexPre {
 __device__ __forceinline__ IndexPre load_index(const LaunchArgs& a, const DevTensor& T,
                                                uint32_t chunk0, uint32_t per_wave) {
   IndexPre p{};
-  if (chunk0 < T.n_chunks) {
-    const uint32_t* index = reinterpret_cast<const uint32_t*>(a.blob + a.index_off);
+  // a wave past the last chunk takes the last one's entries
+  if (chunk0 >= T.n_chunks) chunk0 = (T.n_chunks - 1) / per_wave * per_wave;
+  {
+    typedef __attribute__((address_space(1))) const uint32_t gu32;  // global: no flat access
+    gu32* index = (gu32*)(a.blob + a.index_off);
     const uint32_t g = T.first_chunk + chunk0;
     const uint32_t n_exist = min<uint32_t>(per_wave, T.n_chunks - chunk0);
 #pragma unroll
@@ -272,7 +305,54 @@ __device__ __forceinline__ IndexPre load_index(const LaunchArgs& a, const DevTen
   return p;
 }
 
-template <int L>
+// The tensor of workgroup wg.  A launch's first look at its arguments goes to
+// host memory, so what matters is how many such reads wait for each other (a
+// launch of 2048 chunks of 32 steps: 19 us when they did, 10 us): one vector
+// load compares wg with every tensor's first workgroup at once, and the
+// tensor's fields then arrive together (kTogether), not one by one where they are
+// used.
+template <bool kTogether = true>
+__device__ __forceinline__ DevTensor tensor_of(const LaunchArgs& a, uint32_t wg) {
+  const uint32_t lane = __lane_id();
+  const uint32_t first = a.wg0[lane % kMaxLaunchTensors];
+  const uint32_t before = (uint32_t)__ballot(lane < kMaxLaunchTensors && first <= wg);
+  const uint32_t ti = __builtin_amdgcn_readfirstlane(__popc(before) - 1);
+  constexpr int kWords = sizeof(DevTensor) / 4;
+  static_assert(sizeof(DevTensor) % 8 == 0 && kWords <= 32, "loaded as scalar registers");
+  struct Words {
+    uint32_t v[kWords];
+  };
+  Words w = __builtin_bit_cast(Words, a.t[ti]);
+  if constexpr (kTogether) {
+#pragma unroll
+    for (int i = 0; i < kWords; i += 2) asm volatile("" : "+s"(w.v[i]), "+s"(w.v[i + 1]));
+  }
+  return __builtin_bit_cast(DevTensor, w);
+}
+
+// This wave's place in a launch of workgroups of `waves` waves, `per_wave` chunks
+// each: its chunk and index entries.
+struct WaveOf {
+  uint32_t wave, lane, chunk;
+  IndexPre pre;
+};
+
+__device__ __forceinline__ WaveOf wave_of(const LaunchArgs& a, const DevTensor& T, uint32_t wg,
+                                          uint32_t waves, uint32_t per_wave) {
+  WaveOf w;
+  // the wave index is uniform across the wave; say so, so chunk metadata and
+  // buffer descriptors live in scalar registers
+  w.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  w.lane = __lane_id();
+  w.chunk = ((wg - T.wg0) * waves + w.wave) * per_wave;
+  w.pre = load_index(a, T, w.chunk, per_wave);
+  return w;
+}
+
+// kLate: the index alone says where the record lies, so nothing waits for its
+// header, which check_record looks at once the chunk's other loads are on their
+// way.  Otherwise c.ok is final here.
+template <int L, bool kLate = false>
 __device__ __forceinline__ Chain<L> open_chain(const LaunchArgs& a, const DevTensor& T,
                                                uint32_t chunk0, uint32_t W, uint32_t lane,
                                                uint32_t* ring, const IndexPre& pre) {
@@ -280,6 +360,7 @@ __device__ __forceinline__ Chain<L> open_chain(const LaunchArgs& a, const DevTen
   Chain<L> c;
   const uint8_t* blob = reinterpret_cast<const uint8_t*>(a.blob);
   c.n_exist = min<uint32_t>(kH, T.n_chunks - chunk0);
+  typedef __attribute__((address_space(1))) const uint32_t gu32;  // global: no flat access
   // per-chunk values are wave-uniform; readfirstlane keeps them (and the
   // buffer descriptors built from them) in scalar registers
   uint64_t o[kH + 1];
@@ -298,13 +379,19 @@ __device__ __forceinline__ Chain<L> open_chain(const LaunchArgs& a, const DevTen
     c.A[h] = min<uint32_t>(L, (c.n_c[h] + W - 1) / W);
     bool ok = o[h] >= a.records_off && o[h + 1] <= a.records_end && o[h + 1] >= o[h] + 16;
     if (ok) {
-      const uint32_t* rec = reinterpret_cast<const uint32_t*>(blob + o[h]);
-      c.nw[h] = __builtin_amdgcn_readfirstlane(rec[0]);
-      const uint32_t recA = __builtin_amdgcn_readfirstlane(rec[1]);
-      const uint32_t recN = __builtin_amdgcn_readfirstlane(rec[2]);
+      gu32* rec = (gu32*)(a.blob + o[h]);
       c.wbase[h] = (uint32_t)(o[h] - o[0]) + 16u + (uint32_t)dpad16(4ull * c.A[h]);
-      ok = recA == c.A[h] && recN == c.n_c[h] &&
-           c.wbase[h] + dpad16(2ull * c.nw[h]) == o[h + 1] - o[0];
+      if constexpr (kLate) {
+        // the header's loads stay in flight (check_record reads them)
+        c.rec_hdr[0] = rec[0], c.rec_hdr[1] = rec[1], c.rec_hdr[2] = rec[2];
+        c.len = (uint32_t)(o[h + 1] - o[0]);
+      } else {
+        c.nw[h] = __builtin_amdgcn_readfirstlane(rec[0]);
+        const uint32_t recA = __builtin_amdgcn_readfirstlane(rec[1]);
+        const uint32_t recN = __builtin_amdgcn_readfirstlane(rec[2]);
+        ok = recA == c.A[h] && recN == c.n_c[h] &&
+             c.wbase[h] + dpad16(2ull * c.nw[h]) == o[h + 1] - o[0];
+      }
     }
     c.nunits[h] = ok ? (c.nw[h] + Shape<L>::kUnitWords - 1) / Shape<L>::kUnitWords : 0u;
     c.ok = c.ok && ok;
@@ -342,6 +429,15 @@ __device__ __forceinline__ Chain<L> open_chain(const LaunchArgs& a, const DevTen
   c.rr = make_rsrc(blob + T.raw_off + s0, raw_len);
   c.raw1 = T.per;
   return c;
+}
+
+// The late check of open_chain<64, true>.
+__device__ __forceinline__ void check_record(Chain<64>& c) {
+  if (!c.ok) return;
+  c.nw[0] = __builtin_amdgcn_readfirstlane(c.rec_hdr[0]);
+  c.ok = __builtin_amdgcn_readfirstlane(c.rec_hdr[1]) == c.A[0] &&
+         __builtin_amdgcn_readfirstlane(c.rec_hdr[2]) == c.n_c[0] &&
+         c.wbase[0] + dpad16(2ull * c.nw[0]) == c.len;
 }
 
 // Next unit of half h to issue, or kNoUnit when its stream is done or its
@@ -612,11 +708,13 @@ __device__ void share_idle_wave(const LaunchArgs& a, const DevTensor& T, const S
 // every wave multiplies all decoding waves' operands by its own rows of packed
 // x (see Share).
 template <int G, int L, bool kTiled, int kM = 0, int kMB = 0, int kMR = 16, bool kShare = false,
-          int kWF = 0>
+          int kWF = 0, bool kRing = false, class Build>
 __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTensor& T,
-                                              uint32_t chunk0, uint32_t lane,
+                                              uint32_t chunk_of_wave, uint32_t lane,
                                               const uint2* __restrict__ tab, uint32_t* ring,
-                                              const IndexPre& pre, const Share* sh = nullptr) {
+                                              const IndexPre& pre, Build build,
+                                              const Share* sh = nullptr) {
+  static_assert(!kRing || L == 64, "rings of entries (wc_ring.h): 64 lanes");
   constexpr bool kGemv = kM > 0;   // fused GEMM with kM rows of x, dot products
   constexpr bool kMfma = kMB > 0;  // fused GEMM with kMB blocks of x rows, MFMA
   static_assert(!kShare || (kMfma && kMR == 64), "shared fused GEMM: 64-row tiles");
@@ -666,11 +764,15 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   static_assert(kUnroll % (kPipe * kEvery) == 0 && kUnroll % kGroupsPerRow == 0,
                 "pipeline shape");
 
-  Chain<L> c = open_chain<L>(a, T, chunk0, W, lane, ring, pre);
-  if (!c.ok) {
-    if (lane == 0) report(a, WC_DERR_INDEX);
-    if constexpr (kShare) share_idle_wave<kMB>(a, T, *sh, lane);
-    return;
+  // The record's header, the lane states, the first words and raw bytes are on
+  // their way while the workgroup builds its table (build ends in a barrier).  A
+  // wave past the tensor's last chunk opens that chunk and then leaves.
+  const uint32_t chunk0 = chunk_of_wave < T.n_chunks ? chunk_of_wave : (T.n_chunks - 1) / kH * kH;
+  Chain<L> c = open_chain<L, kRing>(a, T, chunk0, W, lane, ring, pre);
+  [[maybe_unused]] Ring q;
+  if constexpr (kRing) {
+    q.ring = __builtin_amdgcn_readfirstlane(lds_address(ring));
+    q.reset();
   }
   const uint32_t h = kH == 2 ? lane / L : 0u;
   const uint32_t sub = lane % L;
@@ -705,15 +807,13 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   };
   const uint32_t raw_v = (kH == 2 && h ? c.raw1 : 0u) + sub * 8u;   // lane's raw offset
 
-  // prologue: unit 0 committed now, then kPipe units in flight
-  Slot<L> pipe[kPipe];
-  {
-    const Slot<L> s0 = issue(c, h, sub);
-    commit_unit(c, s0, h, sub);
-  }
+  // prologue: unit 0, then kPipe units in flight
+  [[maybe_unused]] Slot<L> first_unit, pipe[kPipe];
+  if constexpr (!kRing) {
+    first_unit = issue(c, h, sub);
 #pragma unroll
-  for (int j = 0; j < kPipe; j++) pipe[j] = issue(c, h, sub);
-  __builtin_amdgcn_wave_barrier();
+    for (int j = 0; j < kPipe; j++) pipe[j] = issue(c, h, sub);
+  }
 
   // raw bytes (8 per lane per row) of the first kRawRows rows (16-bit formats)
   uint2 rq[G == 2 ? kRawRows : 1];
@@ -723,6 +823,21 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
       rq[j] = __builtin_bit_cast(
           uint2, __builtin_amdgcn_raw_buffer_load_b64(c.rr, j * kRawRowBytes + raw_v, 0, 0));
   }
+  build();
+  if constexpr (kRing) check_record(c);
+  if (chunk_of_wave >= T.n_chunks || !c.ok) {
+    if (chunk_of_wave < T.n_chunks && lane == 0) report(a, WC_DERR_INDEX);
+    if constexpr (kRing) q.done();
+    if constexpr (kShare) share_idle_wave<kMB>(a, T, *sh, lane);
+    return;
+  }
+  if constexpr (kRing) {
+    q.start(c.x);
+  } else {
+    commit_unit(c, first_unit, h, sub);
+    __builtin_amdgcn_wave_barrier();
+  }
+
   uint32_t lo[G];   // entries of the dword being assembled
   uint32_t ow[4];   // the row's four output dwords
   uint32_t first_dw = 0;  // row 0's first dword without the carried symbols
@@ -803,13 +918,13 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
     // the first body of full rows: row 0's carried steps are known here
     constexpr bool kFirst = decltype(firstc)::value && j < kGroupsPerRow;
     constexpr int k0 = (j % kGroupsPerRow) * 2;  // first step of this group in its lane-group
-    if constexpr (j % kEvery == 0) {
+    if constexpr (!kRing && j % kEvery == 0) {
       // every kEvery groups: commit the unit loaded kPipe slots ago, load the next
       constexpr int slot = (j / kEvery) % kPipe;
       commit_unit(c, pipe[slot], h, sub);
       pipe[slot] = issue(c, h, sub);
     }
-    __builtin_amdgcn_wave_barrier();
+    if constexpr (!kRing) __builtin_amdgcn_wave_barrier();
     const uint32_t r = g / kGroupsPerRow;
     if constexpr (kShare) {
       if constexpr (j == 0) share_load_x<kMB>(*sh, xrs, r >> 1, xs);
@@ -848,9 +963,12 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
     for (int k = k0; k < k0 + 2; k++) {
       if (kFirst && uint32_t(k) < kCK)
         lo[k % G] = 0u;  // carried in the start state: not coded
+      else if constexpr (kRing)
+        lo[k % G] = q.template step<!kTail>(k < nv && k >= kc);
       else
         lo[k % G] = step<!kTail, L, !(kGemv || kMfma)>(c, tab, k < nv && k >= kc, h);
     }
+    if constexpr (kRing) q.check();
     if constexpr ((k0 + 2) % G == 0) {
       constexpr int d = (k0 + 1) / G;             // the dword these G steps complete
       uint32_t raw2 = 0;
@@ -1137,6 +1255,12 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
 
   // --- end-of-chunk checks: every lane back at its start, every word consumed
   uint32_t bits = 0;
+  if constexpr (kRing) {
+    const uint32_t s0 = first_slot(tab, T.kind, q.e.x >> 24);
+    c.x = q.state(tab[s0].x & 0xFFFFFFu, s0);
+    c.cursor[0] = q.cur / 8u;
+    q.done();
+  }
   const uint32_t A_h = kH == 2 && h ? c.A[kH - 1] : c.A[0];
   if constexpr (kCK > 0) {
     // the carried symbols: the lane's first min(kCK, n0) symbols from D
@@ -1149,7 +1273,10 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
       uint32_t lc[G];
 #pragma unroll
       for (int t = 0; t < G; t++)
-        lc[t] = uint32_t(t) < kl ? ((D >> (kCB * t)) & ((1u << kCB) - 1u)) << 24 : 0u;
+        lc[t] = uint32_t(t) < kl
+                    ? table_symbol(G == 2 ? kSplit16 : kByte, (D >> (kCB * t)) & ((1u << kCB) - 1u))
+                          << 24
+                    : 0u;
       const uint32_t dw = first_dw | assemble<G>(lc, 0u);
       // the lane's first dword again, now whole (only its valid bytes)
       const uint32_t nb = min(4u, n0 * 4u / G + (G == 8 ? (n0 & 1u) : 0u));
@@ -1205,6 +1332,13 @@ inline void fill_common(LaunchArgs& args, const wc::BlobPriv& P, const void* dev
   args.records_off = P.records_off;
   args.records_end = P.size;
   args.err = reinterpret_cast<uint64_t>(dev_err);
+}
+
+// The launch's tensors are all in args.t: their count and first workgroups.
+inline void set_tensors(LaunchArgs& args, uint32_t n) {
+  args.n_tensors = n;
+  for (uint32_t k = 0; k < uint32_t(kMaxLaunchTensors); k++)
+    args.wg0[k] = k < n ? args.t[k].wg0 : 0xFFFFFFFFu;
 }
 
 }  // namespace

@@ -42,21 +42,12 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk = (wg - T.wg0) * kWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk >= T.n_chunks) return;
-  decode_chunks<G, 64, true, kM, kMB, kMR, false, kFp8 ? 1 : 0>(a, T, chunk, lane, tab, ring[wave],
-                                                                pre);
+  const DevTensor T = tensor_of(a, blockIdx.x);
+  const WaveOf w = wave_of(a, T, blockIdx.x, kWaves, 1u);
+  decode_chunks<G, 64, true, kM, kMB, kMR, false, kFp8 ? 1 : 0>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<kThreads>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 // The same fused decode-GEMM for fp8 e5m2 weights on 16-row tiles: kMB blocks
@@ -66,20 +57,12 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_e5m2_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk = (wg - T.wg0) * kWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk >= T.n_chunks) return;
-  decode_chunks<4, 64, true, 0, kMB, 16, false, 2>(a, T, chunk, lane, tab, ring[wave], pre);
+  const DevTensor T = tensor_of(a, blockIdx.x);
+  const WaveOf w = wave_of(a, T, blockIdx.x, kWaves, 1u);
+  decode_chunks<4, 64, true, 0, kMB, 16, false, 2>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<kThreads>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 // The same fused decode-GEMM for MXFP4 weights (e2m1 nibbles, 16-row tiles):
@@ -90,20 +73,12 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_mx_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk = (wg - T.wg0) * kWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk >= T.n_chunks) return;
-  decode_chunks<8, 64, true, 0, kMB, 16, false, 3>(a, T, chunk, lane, tab, ring[wave], pre);
+  const DevTensor T = tensor_of(a, blockIdx.x);
+  const WaveOf w = wave_of(a, T, blockIdx.x, kWaves, 1u);
+  decode_chunks<8, 64, true, 0, kMB, 16, false, 3>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<kThreads>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 // The same for MXFP4 codes coded as bytes (WC_U8 tensors holding the packed
@@ -113,20 +88,12 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_mxb_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk = (wg - T.wg0) * kWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk >= T.n_chunks) return;
-  decode_chunks<4, 64, true, 0, kMB, 16, false, 3>(a, T, chunk, lane, tab, ring[wave], pre);
+  const DevTensor T = tensor_of(a, blockIdx.x);
+  const WaveOf w = wave_of(a, T, blockIdx.x, kWaves, 1u);
+  decode_chunks<4, 64, true, 0, kMB, 16, false, 3>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<kThreads>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 // The fused decode-GEMM for group-quantised int4 weights (codes as bytes,
@@ -136,20 +103,12 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_w4_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk = (wg - T.wg0) * kWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk >= T.n_chunks) return;
-  decode_chunks<4, 64, true, 0, kMB, 16, false, 4>(a, T, chunk, lane, tab, ring[wave], pre);
+  const DevTensor T = tensor_of(a, blockIdx.x);
+  const WaveOf w = wave_of(a, T, blockIdx.x, kWaves, 1u);
+  decode_chunks<4, 64, true, 0, kMB, 16, false, 4>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<kThreads>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 // The same for int4 codes as nibble symbols (WC_U4 tensors).
@@ -158,20 +117,12 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_w4n_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t lane = __lane_id();
-  const uint32_t chunk = (wg - T.wg0) * kWaves + wave;
-  const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (chunk >= T.n_chunks) return;
-  decode_chunks<8, 64, true, 0, kMB, 16, false, 4>(a, T, chunk, lane, tab, ring[wave], pre);
+  const DevTensor T = tensor_of(a, blockIdx.x);
+  const WaveOf w = wave_of(a, T, blockIdx.x, kWaves, 1u);
+  decode_chunks<8, 64, true, 0, kMB, 16, false, 4>(a, T, w.chunk, w.lane, tab, ring[w.wave], w.pre, [&] {
+    build_table<kThreads>(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  });
 }
 
 // The shared fused GEMM: workgroup = (pass over 256 kXB rows of x, band of 64
@@ -186,10 +137,7 @@ __global__ __launch_bounds__(kThreads) void wc_gemm_kernel(LaunchArgs a) {
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
   __shared__ u32x4 frag[kWaves * 2 * 64];
   const uint32_t wg = blockIdx.x;
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  const DevTensor& T = a.t[ti];
+  const DevTensor T = tensor_of(a, wg);
   const uint32_t tid = threadIdx.x;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t lane = __lane_id();
@@ -218,12 +166,17 @@ __global__ __launch_bounds__(kThreads) void wc_gemm_kernel(LaunchArgs a) {
   const bool decodes = wave < s.n_act;
   const uint32_t chunk = band * T.ntc + seg * kWaves + (decodes ? wave : 0u);
   const IndexPre pre = load_index(a, T, chunk, 1u);
-  build_table(a, T, tab, cum, tid);
-  __syncthreads();
-  if (decodes)
-    decode_chunks<2, 64, true, 0, kXB, 64, true>(a, T, chunk, lane, tab, ring[wave], pre, &s);
-  else
+  auto build = [&] {
+    build_table(a, T, tab, cum, threadIdx.x);
+    __syncthreads();
+  };
+  if (decodes) {
+    decode_chunks<2, 64, true, 0, kXB, 64, true>(a, T, chunk, lane, tab, ring[wave], pre, build,
+                                                 &s);
+  } else {
+    build();
     share_idle_wave<kXB>(a, T, s, lane);
+  }
 }
 
 }  // namespace
@@ -371,7 +324,7 @@ wc_status launch_jobs(const wc::BlobPriv& P, const void* dev_blob, uint32_t n,
       nt++;
     }
     if (!nt) continue;
-    args.n_tensors = nt;
+    set_tensors(args, nt);
     args.m = m;
     if (wide) {
       if (!wc::gemv_wide_launch(wide_kind, &args, sizeof args, wgs, st)) return WC_EHIP;
@@ -489,7 +442,7 @@ extern "C" wc_status wc_gemm_i8(const wc_blob* desc, const void* dev_blob, uint3
     args.t[i].x = reinterpret_cast<uint64_t>(dev_x[i]);
     wgs += uint32_t((T.n_chunks + per_wg - 1) / per_wg);
   }
-  args.n_tensors = n;
+  set_tensors(args, n);
   args.m = m;
   const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (wide) return wc::gemv_wide_launch(0, &args, sizeof args, wgs, st) ? WC_OK : WC_EHIP;
@@ -554,7 +507,7 @@ extern "C" wc_status wc_gemv_mx(const wc_blob* desc, const void* dev_blob, uint3
       nt++;
     }
     if (!nt) continue;
-    args.n_tensors = nt;
+    set_tensors(args, nt);
     args.m = m;
     if (wide) {
       if (!wc::gemv_wide_launch(3, &args, sizeof args, wgs, st)) return WC_EHIP;
@@ -633,7 +586,7 @@ extern "C" wc_status wc_gemv_w4(const wc_blob* desc, const void* dev_blob, uint3
       nt++;
     }
     if (!nt) continue;
-    args.n_tensors = nt;
+    set_tensors(args, nt);
     args.m = m;
     if (wide) {
       if (!wc::gemv_wide_launch(4, &args, sizeof args, wgs, st)) return WC_EHIP;

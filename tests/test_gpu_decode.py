@@ -313,3 +313,34 @@ def test_tiled_full_size_70b_layer(dev):
             assert np.array_equal(got[rs, cs], ref[rs, cs]), (t, c)
     del outs
     torch.cuda.empty_cache()
+
+
+def _rare_symbols(dtype, chunks):
+    """Bytes whose table is nearly one symbol, with chunks of nothing but rare
+    ones: 12 bits a symbol there, the most words a step can take."""
+    rng = np.random.default_rng(chunks)
+    d = np.zeros((chunks, 1024), np.uint8)
+    rare = rng.permutation(chunks)[:max(1, chunks // 64)]
+    d[rare] = rng.integers(1, 256, (rare.size, 1024))
+    return d.reshape(-1).view(np.uint16) if dtype in ("bf16", "fp16") else d.reshape(-1)
+
+
+@pytest.mark.parametrize("tile", [None, (4, 0), (4, 1)])
+@pytest.mark.parametrize("dtype", ["bf16", "u8", "u4"])
+@pytest.mark.parametrize("chunks", [1, 1024, 1025, 2048, 2049])
+def test_launches_around_the_small_kernels_limits(dev, chunks, dtype, tile):
+    """Up to four, up to eight and more 64-lane chunks to a compute unit (256 on
+    an MI355X) run on different kernels: whole and ragged chunks of 1 KiB, byte
+    runs and both tile orders, every symbol width, words at the highest rate."""
+    say("small kernel", chunks, dtype, tile)
+    d = _rare_symbols(dtype, chunks)
+    if tile is None:
+        d = d[: d.size - (77 if chunks > 1 else 0)]
+        entries, kw = [(dtype, d)], {}
+    else:
+        cols = {"bf16": 128, "u8": 256, "u4": 512}[dtype]  # 4 x cols symbols: 1 KiB
+        entries = [(dtype, d, (4 * chunks, cols))]
+        kw = {"tile": (4, cols), "tile_order": tile[1]}
+    blob = wc.encode(entries, chunk_bytes=1024, **kw)
+    assert blob.n_chunks == chunks
+    check_exact([(dtype, d)], blob, gpu_decode(blob, dev))
