@@ -257,7 +257,8 @@ wc_blob* make_handle(BlobPriv&& bp) {
 // ---------------------------------------------------------------------------
 // Statistics from histograms (Sec. II-B).
 
-void finish_stats(uint32_t dt, uint64_t n, const uint64_t* joint16, wc_stats* out) {
+void finish_stats(uint32_t dt, uint64_t n, const uint64_t* joint16, uint32_t n_joint,
+                  wc_stats* out) {
   out->n_fields = has_raw(dt) ? 2 : 1;
   out->alphabet[0] = alphabet_of(dt);
   out->alphabet[1] = has_raw(dt) ? 256 : 0;
@@ -270,15 +271,25 @@ void finish_stats(uint32_t dt, uint64_t n, const uint64_t* joint16, wc_stats* ou
   }
   out->bound_bytes = bound;
   out->bound_bytes_raw8 = double(n) * out->H[0] / 8.0 + (has_raw(dt) ? double(n) : 0.0);
-  out->H_joint16 = joint16 ? entropy_bits(joint16, 65536) : NAN;
+  out->H_joint16 = joint16 ? entropy_bits(joint16, n_joint) : NAN;
 }
 
-void split_word_counts(const uint64_t* joint16, wc_stats* out) {
-  for (uint32_t w = 0; w < 65536; w++) {
-    if (!joint16[w]) continue;
-    out->hist[0][(w >> 7) & 0xFF] += joint16[w];
-    out->hist[1][((w >> 8) & 0x80) | (w & 0x7F)] += joint16[w];
+uint32_t split_word_counts(uint64_t* joint16, wc_stats* out) {
+  uint32_t n = 0;
+  for (uint32_t w0 = 0; w0 < 65536; w0 += 8) {
+    // most words of a tensor of weights never occur: eight at a time
+    uint64_t any = 0;
+    for (uint32_t k = 0; k < 8; k++) any |= joint16[w0 + k];
+    if (!any) continue;
+    for (uint32_t w = w0; w < w0 + 8; w++) {
+      const uint64_t c = joint16[w];
+      if (!c) continue;
+      out->hist[0][(w >> 7) & 0xFF] += c;
+      out->hist[1][((w >> 8) & 0x80) | (w & 0x7F)] += c;
+      joint16[n++] = c;
+    }
   }
+  return n;
 }
 
 // ---------------------------------------------------------------------------
@@ -491,7 +502,7 @@ wc_status wc_analyze(const wc_tensor* t, wc_stats* out) {
         for (uint64_t i = s0; i < s1; i++) h16[src[2 * i] | (uint32_t(src[2 * i + 1]) << 8)]++;
       }
     }
-    finish_stats(dt, n, has_raw(dt) ? h16.data() : nullptr, out);
+    finish_stats(dt, n, has_raw(dt) ? h16.data() : nullptr, 65536, out);
     return WC_OK;
   } catch (const std::bad_alloc&) {
     return WC_ENOMEM;

@@ -414,3 +414,26 @@ def test_model_family_layer(dev, model):
         assert raw.tobytes() == oracle.encode(host)
     del tens, blob
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("words", [1, 65527, 65528, 65529, 32768 * 2 + 5, 3_000_001, 40_000_003])
+@pytest.mark.parametrize("kind", ["constant", "neighbours", "hot late", "random"])
+def test_word_counts_where_16_bit_counters_overflow(dev, words, kind):
+    """The whole-word histogram counts in 16-bit counters: one bin with every
+    word, the two bins that share a dword, a bin that only fills up after the
+    first piece looked harmless, and words spread over all bins, around the
+    piece that is always safe and over several workgroups, ragged."""
+    say("word counts", words, kind)
+    rng = np.random.default_rng(words)
+    w = rng.integers(0, 65536, words).astype(np.uint16)
+    if kind == "constant":
+        w[:] = 0xBE01
+    elif kind == "neighbours":
+        w = (0x3C00 + (w & 1)).astype(np.uint16)
+    elif kind == "hot late":
+        w[65528:] = 0x7FFF
+    want = wc.analyze("bf16", w)
+    got = wc.analyze_device("bf16", torch.from_numpy(w.view(np.uint8)).to(dev))
+    assert np.array_equal(got["hist"][0], want["hist"][0])
+    assert np.array_equal(got["hist"][1], want["hist"][1])
+    assert got["H_joint16"] == want["H_joint16"] and got["H"] == want["H"]
