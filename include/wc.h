@@ -373,10 +373,10 @@ wc_status wc_gemm_workspace_bytes(const wc_blob* desc, uint32_t n, const uint32_
 /* wc_gemm -- the fused decode-GEMM of wc_gemv for any batch: m = 1..4096 rows
  * of x (Alg. 1 / 3; Sec. V, the batch-size regime).  Up to m = 64 it is
  * wc_gemv (the workspace is not used).  Above, the weights are decoded once
- * per pass of 256 x rows: the 8 waves of a workgroup decode 8 consecutive
- * tiles of one band of 64 W rows, exchange each pair of decoded wave rows
- * (64 W rows x 16 columns, two v_mfma_f32_32x32x16_bf16 B operands) through
- * LDS, and each wave multiplies all of them by its own 32 rows of x.  x is
+ * per pass of 256 x rows (512 for m > 256): 8 waves of a workgroup decode 8
+ * consecutive tiles of one band of 64 W rows and leave each pair of decoded wave
+ * rows (64 W rows x 16 columns, two v_mfma_f32_32x32x16_bf16 B operands) in LDS;
+ * 8 more waves multiply all of them by their own 32 or 64 rows of x.  x is
  * first packed into the workspace in MFMA operand order (one kernel per
  * distinct x, on the same stream).  Jobs, arguments and y as for wc_gemv;
  * above m = 64 every tensor must have 64-row tiles of at least 16 columns
@@ -384,12 +384,12 @@ wc_status wc_gemm_workspace_bytes(const wc_blob* desc, uint32_t n, const uint32_
  *   dev_workspace  device memory of at least wc_gemm_workspace_bytes bytes,
  *                  256-byte aligned, owned by the caller; overwritten; calls
  *                  sharing a workspace must not overlap in time.
- * When to use it: every further pass of 256 x rows decodes the weights again,
- * so the fused call pays off up to about 256 rows.  Above that, decode the
+ * When to use it: every further pass of x rows decodes the weights again,
+ * so the fused call pays off up to about 512 rows.  Above that, decode the
  * weights once with wc_decode and multiply with a library GEMM: on one
  * MI355X, for the seven products of a Llama-3-70B layer, the fused call took
- * 0.918 ms at m = 256 against 1.356 ms decode-then-multiply, but 1.779 ms at
- * m = 512 against 1.468 ms, and 3.499 ms at m = 1024 against 1.978 ms.  The
+ * 0.907 ms at m = 256 against 1.339 ms decode-then-multiply and 1.366 ms at
+ * m = 512 against 1.455 ms, but 2.820 ms at m = 1024 against 1.967 ms.  The
  * call does not switch by itself.
  * Asynchronous; allocates nothing.  Returns WC_EINVAL (argument, or a
  * workspace too small or misaligned) or WC_EUNSUPPORTED (a tensor the path

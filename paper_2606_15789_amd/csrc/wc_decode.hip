@@ -92,10 +92,10 @@ __global__ __launch_bounds__(kChunks * 128) void wc_decode_small_kernel(LaunchAr
   auto run = [&](auto gc) {
     constexpr int G = decltype(gc)::value;
     if (T.tiled)
-      decode_chunks<G, 64, true, 0, 0, 16, false, 0, true>(a, T, chunk, lane, tab, ring, pre,
+      decode_chunks<G, 64, true, 0, 0, 16, false, 0, FedRing>(a, T, chunk, lane, tab, ring, pre,
                                                            build);
     else
-      decode_chunks<G, 64, false, 0, 0, 16, false, 0, true>(a, T, chunk, lane, tab, ring, pre,
+      decode_chunks<G, 64, false, 0, 0, 16, false, 0, FedRing>(a, T, chunk, lane, tab, ring, pre,
                                                             build);
   };
   switch (T.kind) {

@@ -48,6 +48,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "wc_internal.h"
@@ -245,6 +246,8 @@ template <int L>
 struct Chain {
   static constexpr int kH = 64 / L;
   __amdgpu_buffer_rsrc_t rs;  // the chunks' records
+  uint64_t rec;               // their address and bytes
+  uint32_t rec_bytes;
   uint32_t rec_hdr[3], len;   // the record's header words, loaded late, and its bytes
   __amdgpu_buffer_rsrc_t rr;  // the chunks' raw bytes (16-bit formats)
   __amdgpu_buffer_rsrc_t os;  // the chunks' decoded bytes
@@ -397,7 +400,9 @@ __device__ __forceinline__ Chain<L> open_chain(const LaunchArgs& a, const DevTen
     c.ok = c.ok && ok;
     end = o[h + 1];
   }
-  c.rs = make_rsrc(blob + o[0], c.ok ? (uint32_t)(end - o[0]) : 0u);
+  c.rec = a.blob + o[0];
+  c.rec_bytes = c.ok ? (uint32_t)(end - o[0]) : 0u;
+  c.rs = make_rsrc(blob + o[0], c.rec_bytes);
   c.rec1 = kH == 2 ? (uint32_t)(o[1] - o[0]) : 0u;
   // lane -> half h, lane within the half
   const uint32_t h = kH == 2 ? lane / L : 0u;
@@ -565,15 +570,26 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// The shared fused GEMM, for many rows of x on column-block tiles of 64 rows:
-// the waves of a workgroup decode up to kWaves consecutive tiles of one band
-// of 64 W rows (one tile each), so every weight is decoded once per pass over
-// the rows of x.  After each pair of wave rows a decoding wave leaves its two
-// v_mfma_f32_32x32x16_bf16 B operands (64 W rows x 16 columns) in LDS, and
-// every wave multiplies all of them by its own kXB blocks of 32 x rows.
+// The shared fused GEMM, for many rows of x on column-block tiles of 64 rows.
+// The first kShareTiles waves of a workgroup decode that many consecutive tiles of
+// one band of 64 W rows (one tile each); the other waves multiply.  After each
+// pair of wave rows a decoding wave leaves its two v_mfma_f32_32x32x16_bf16 B
+// operands (64 W rows x 16 columns) in one half of an LDS buffer, and while the
+// next pair is decoded into the other half, every multiplying wave takes all of
+// them times its own kXB blocks of 32 x rows, so that the matrix cores work beside
+// the decode.  Each wave publishes how many pairs it has written or multiplied,
+// and the waves wait for each other's counts, not for all waves at a barrier: a
+// decoding wave that commits words (wc_ring.h) in one pair may catch up in the next
+// (2 % on the 8B layer at m = 80).  The waits end: the pair a wave waits for never
+// waits for a later one, and a wave that leaves early publishes kShareAll.
+constexpr int kShareTiles = 8;
+constexpr int kShareMultiply = 8;  // multiplying waves
+constexpr uint32_t kShareAll = 0x7FFFFFFFu;
 struct Share {
-  u32x4* frag;     // LDS [kWaves][2][64]: each wave's B operands of the current pair
-  uint32_t wave;   // this wave's slot
+  u32x4* frag;     // LDS [2][kShareTiles][2][64]: the tiles' B operands of two pairs
+  uint32_t pairs_written;     // LDS address of [kShareTiles] counts: pairs of each tile written
+  uint32_t pairs_multiplied;  // and of [kShareMultiply]: pairs each multiplying wave is past
+  uint32_t wave;   // decoding: this wave's tile; multiplying: its blocks of x rows
   uint32_t n_act;  // waves of the workgroup that decode a tile (operands per pair)
   uint32_t xoff;   // this lane's byte offset in packed x: tile 0, pair 0, x block 0
   uint32_t xtile;  // packed x bytes between two consecutive tiles
@@ -585,48 +601,26 @@ struct Share {
   uint64_t N;      // columns of y (rows of W)
 };
 
-// LDS writes of every wave before the barrier are seen by every wave after it;
-// global loads in flight stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+// Wait until all n counts (a power of two, at most 64) at LDS address `counts` have
+// reached `least`.
+__device__ __forceinline__ void share_wait(uint32_t counts, uint32_t n, uint32_t least) {
+  const uint32_t at = counts + 4u * (__lane_id() & (n - 1u));
+  while (__ballot(*(lds_counter*)(uintptr_t)at < least)) __builtin_amdgcn_s_sleep(1);
+  asm volatile("" ::: "memory");
 }
 
-// A operands of one pair for every decoding wave's tile, from packed x: lane l
-// holds x row (first + l mod 32), columns 16 pair + 8 (l div 32) .. of the
-// tile; absent tiles and x blocks load nothing.
+// A operand of one tile and pair, from packed x: lane l holds x row (first + 32 xb +
+// l mod 32), columns 16 pair + 8 (l div 32) .. of the tile; absent x blocks load
+// nothing.
 template <int kXB>
 __device__ __forceinline__ void share_load_x(const Share& s, __amdgpu_buffer_rsrc_t xrs,
-                                             uint32_t pair, u32x4 (&xs)[kWaves][kXB]) {
+                                             uint32_t tile, uint32_t pair, u32x4 (&x)[kXB]) {
 #pragma unroll
-  for (int f = 0; f < kWaves; f++)
-#pragma unroll
-    for (int xb = 0; xb < kXB; xb++) {
-      const bool use = uint32_t(f) < s.n_act && 32u * xb < s.mrows;
-      const uint32_t off = use ? s.xoff + f * s.xtile + xb * s.xblk + pair * 1024u : kFarOffset;
-      xs[f][xb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, off, 0, 0));
-    }
-}
-
-// acc[xb][nb] += x block xb times W rows 32 nb .. 32 nb + 31 of every tile's pair
-template <int kXB>
-__device__ __forceinline__ void share_mma(const Share& s, uint32_t lane,
-                                          const u32x4 (&xs)[kWaves][kXB],
-                                          f32x16 (&acc)[kXB][2]) {
-  if (s.mrows == 0) return;  // no rows of x in this pass: no operand to read
-#pragma unroll
-  for (int f = 0; f < kWaves; f++) {
-    if (uint32_t(f) >= s.n_act) break;
-    const bf16x8 b0 = __builtin_bit_cast(bf16x8, s.frag[(2 * f) * 64 + lane]);
-    const bf16x8 b1 = __builtin_bit_cast(bf16x8, s.frag[(2 * f + 1) * 64 + lane]);
-#pragma unroll
-    for (int xb = 0; xb < kXB; xb++) {
-      if (32u * xb >= s.mrows) break;
-      const bf16x8 A = __builtin_bit_cast(bf16x8, xs[f][xb]);
-      acc[xb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, b0, acc[xb][0], 0, 0, 0);
-      acc[xb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, b1, acc[xb][1], 0, 0, 0);
-    }
+  for (int xb = 0; xb < kXB; xb++) {
+    const uint32_t off = 32u * xb < s.mrows
+                             ? s.xoff + tile * s.xtile + xb * s.xblk + pair * 1024u
+                             : kFarOffset;
+    x[xb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xrs, off, 0, 0));
   }
 }
 
@@ -648,24 +642,46 @@ __device__ __forceinline__ void share_store(const Share& s, uint32_t lane,
       }
 }
 
-// A wave of the workgroup with no tile to decode (or whose tile's index entry
-// is bad): it takes part in every pair's barriers and multiplies the decoding
-// waves' operands by its own rows of x.
+// A multiplying wave: acc[xb][nb] += x block xb times W rows 32 nb .. 32 nb + 31 of
+// every tile, pair after pair.  x is loaded kAhead tiles ahead, across the pairs.
 template <int kXB>
-__device__ void share_idle_wave(const LaunchArgs& a, const DevTensor& T, const Share& s,
-                                uint32_t lane) {
+__device__ __forceinline__ void share_multiply(const LaunchArgs& a, const DevTensor& T,
+                                               const Share& s, uint32_t lane) {
+  if (s.mrows == 0) {  // no rows of x in this pass
+    set_counter(s.pairs_multiplied + 4u * s.wave, kShareAll);
+    return;
+  }
+  constexpr int kAhead = 4;
+  static_assert(kShareTiles % kAhead == 0, "a tile's place in x is known at compile time");
   const uint32_t K = T.ntc << T.log_tc;
   const __amdgpu_buffer_rsrc_t xrs =
       make_rsrc(reinterpret_cast<const void*>(T.x), ((a.m + 31u) & ~31u) * K * 2u);
   f32x16 acc[kXB][2];
 #pragma unroll
   for (int xb = 0; xb < kXB; xb++) acc[xb][0] = acc[xb][1] = f32x16{};
-  u32x4 xs[kWaves][kXB];
+  u32x4 x[kAhead][kXB];
+#pragma unroll
+  for (int f = 0; f < kAhead; f++) share_load_x<kXB>(s, xrs, f, 0, x[f]);
   for (uint32_t p = 0; p < s.pairs; p++) {
-    share_load_x<kXB>(s, xrs, p, xs);
-    lds_barrier();
-    share_mma<kXB>(s, lane, xs, acc);
-    lds_barrier();
+    share_wait(s.pairs_written, kShareTiles, p + 1);
+    const u32x4* frag = s.frag + (p & 1u) * (kShareTiles * 2 * 64);
+#pragma unroll
+    for (int f = 0; f < kShareTiles; f++) {
+      if (uint32_t(f) < s.n_act) {
+        const bf16x8 b0 = __builtin_bit_cast(bf16x8, frag[(2 * f) * 64 + lane]);
+        const bf16x8 b1 = __builtin_bit_cast(bf16x8, frag[(2 * f + 1) * 64 + lane]);
+#pragma unroll
+        for (int xb = 0; xb < kXB; xb++) {
+          const bf16x8 A = __builtin_bit_cast(bf16x8, x[f % kAhead][xb]);
+          acc[xb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, b0, acc[xb][0], 0, 0, 0);
+          acc[xb][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, b1, acc[xb][1], 0, 0, 0);
+        }
+      }
+      // the tile kAhead on: of this pair, or of the next (past the last pair: unused)
+      share_load_x<kXB>(s, xrs, (f + kAhead) % kShareTiles, f + kAhead < kShareTiles ? p : p + 1,
+                        x[f % kAhead]);
+    }
+    set_counter(s.pairs_multiplied + 4u * s.wave, p + 1);
   }
   share_store<kXB>(s, lane, acc, reinterpret_cast<float*>(T.dst));
 }
@@ -703,18 +719,18 @@ __device__ void share_idle_wave(const LaunchArgs& a, const DevTensor& T, const S
 // keep row r, lanes 32..63 take row r + 1 of the same W rows), which share
 // one A operand of x, so every x value loaded feeds 64 W rows.
 //
-// kShare (with kMR = 64): the shared fused GEMM.  The two B operands of each
-// pair go to this wave's slot in LDS instead, and after a workgroup barrier
-// every wave multiplies all decoding waves' operands by its own rows of packed
-// x (see Share).
+// kShare (with kMR = 64): a decoding wave of the shared fused GEMM.  The two B
+// operands of each pair go to this wave's slot in LDS, for the multiplying waves
+// (see Share).
 template <int G, int L, bool kTiled, int kM = 0, int kMB = 0, int kMR = 16, bool kShare = false,
-          int kWF = 0, bool kRing = false, class Build>
+          int kWF = 0, class RingOf = void, class Build>
 __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTensor& T,
                                               uint32_t chunk_of_wave, uint32_t lane,
                                               const uint2* __restrict__ tab, uint32_t* ring,
                                               const IndexPre& pre, Build build,
                                               const Share* sh = nullptr) {
-  static_assert(!kRing || L == 64, "rings of entries (wc_ring.h): 64 lanes");
+  constexpr bool kRing = !std::is_void_v<RingOf>;  // words as table entries (wc_ring.h)
+  static_assert(!kRing || L == 64, "rings of entries: 64 lanes");
   constexpr bool kGemv = kM > 0;   // fused GEMM with kM rows of x, dot products
   constexpr bool kMfma = kMB > 0;  // fused GEMM with kMB blocks of x rows, MFMA
   static_assert(!kShare || (kMfma && kMR == 64), "shared fused GEMM: 64-row tiles");
@@ -769,11 +785,11 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   // wave past the tensor's last chunk opens that chunk and then leaves.
   const uint32_t chunk0 = chunk_of_wave < T.n_chunks ? chunk_of_wave : (T.n_chunks - 1) / kH * kH;
   Chain<L> c = open_chain<L, kRing>(a, T, chunk0, W, lane, ring, pre);
-  [[maybe_unused]] Ring q;
-  if constexpr (kRing) {
-    q.ring = __builtin_amdgcn_readfirstlane(lds_address(ring));
-    q.reset();
-  }
+  [[maybe_unused]] std::conditional_t<kRing, RingOf, Entry> q;
+  if constexpr (kRing)
+    q.open(__builtin_amdgcn_readfirstlane(lds_address(ring)), c.rs,
+           ru4{(uint32_t)c.rec, (uint32_t)(c.rec >> 32) & 0xFFFFu, c.rec_bytes, 0x00020000u},
+           c.wbase[0], lane);
   const uint32_t h = kH == 2 ? lane / L : 0u;
   const uint32_t sub = lane % L;
   // rows every lane of every half decodes in full, and rows in total
@@ -827,8 +843,8 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   if constexpr (kRing) check_record(c);
   if (chunk_of_wave >= T.n_chunks || !c.ok) {
     if (chunk_of_wave < T.n_chunks && lane == 0) report(a, WC_DERR_INDEX);
-    if constexpr (kRing) q.done();
-    if constexpr (kShare) share_idle_wave<kMB>(a, T, *sh, lane);
+    if constexpr (kRing) q.close();
+    if constexpr (kShare) set_counter(sh->pairs_written + 4u * sh->wave, kShareAll);
     return;
   }
   if constexpr (kRing) {
@@ -860,8 +876,6 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   typedef __attribute__((ext_vector_type(4))) int i32x4;
   facc macc[kMfma && !kShare && !kInt8 ? kMB : 1][kNB];
   i32x4 iacc[kInt8 ? kMB : 1];                   // int8 GEMM: 16 x 16 int32 sums per block
-  f32x16 sacc[kShare ? kMB : 1][2];        // shared GEMM: this wave's x blocks x 64 W rows
-  u32x4 xs[kShare ? kWaves : 1][kShare ? kMB : 1];  // shared GEMM: A operands of the pair
   uint32_t prev[kMR == 64 ? 4 : 1];             // 64-row tiles: the even row's dwords
   u4v xa[kMfma ? kMB : 1];
   u4v xa2[kFp8W ? kMB : 1];  // fp8 weights: x columns 8..15 of the lane's 16
@@ -871,15 +885,11 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   uint32_t i4z = 0;   // int4: its zero point
   // the x rows (fused GEMM on the matrix cores): a.m rows of K bf16
   const uint32_t K = (T.ntc << T.log_tc) * kEPS;  // columns of W = length of an x row
-  // (the shared GEMM reads packed x: rows rounded up to blocks of 32)
   const __amdgpu_buffer_rsrc_t xrs = make_rsrc(
       reinterpret_cast<const void*>(T.x),
-      kShare ? ((a.m + 31u) & ~31u) * K * 2u : (kMfma ? a.m * K * kXB : 0u));
+      kMfma && !kShare ? a.m * K * kXB : 0u);
   uint32_t xoff = 0, xblk = 0;
-  if constexpr (kShare) {
-#pragma unroll
-    for (int xb = 0; xb < kMB; xb++) sacc[xb][0] = sacc[xb][1] = f32x16{};
-  } else if constexpr (kMfma) {
+  if constexpr (kMfma && !kShare) {
 #pragma unroll
     for (int mb = 0; mb < kMB; mb++) {
       iacc[kInt8 ? mb : 0] = i32x4{};
@@ -926,9 +936,6 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
     }
     if constexpr (!kRing) __builtin_amdgcn_wave_barrier();
     const uint32_t r = g / kGroupsPerRow;
-    if constexpr (kShare) {
-      if constexpr (j == 0) share_load_x<kMB>(*sh, xrs, r >> 1, xs);
-    }
     if constexpr (kMfma && !kShare && j % kGroupsPerRow == 0 &&
                   (kMR != 64 || j < kGroupsPerRow)) {
       // the A operands of this wave row (512 / kMR columns of each x row; for
@@ -964,11 +971,11 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
       if (kFirst && uint32_t(k) < kCK)
         lo[k % G] = 0u;  // carried in the start state: not coded
       else if constexpr (kRing)
-        lo[k % G] = q.template step<!kTail>(k < nv && k >= kc);
+        lo[k % G] = q.template next<!kTail>(k < nv && k >= kc);
       else
         lo[k % G] = step<!kTail, L, !(kGemv || kMfma)>(c, tab, k < nv && k >= kc, h);
     }
-    if constexpr (kRing) q.check();
+    if constexpr (kRing) q.template check<j>();
     if constexpr ((k0 + 2) % G == 0) {
       constexpr int d = (k0 + 1) / G;             // the dword these G steps complete
       uint32_t raw2 = 0;
@@ -1001,13 +1008,14 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
             b1[d] = sw[1];  // W rows 32..63
           }
           if constexpr (kShare) {
-            // this wave's operands to every wave of the workgroup, then all of them
-            // times this wave's rows of x; the second barrier frees the slots
-            sh->frag[(2 * sh->wave) * 64 + lane] = u32x4{b0[0], b0[1], b0[2], b0[3]};
-            sh->frag[(2 * sh->wave + 1) * 64 + lane] = u32x4{b1[0], b1[1], b1[2], b1[3]};
-            lds_barrier();
-            share_mma<kMB>(*sh, lane, xs, sacc);
-            lds_barrier();
+            // this wave's operands to the multiplying waves, once they have left this
+            // half of the buffer
+            const uint32_t pair = r >> 1;
+            if (pair >= 2) share_wait(sh->pairs_multiplied, kShareMultiply, pair - 1);
+            u32x4* frag = sh->frag + (pair & 1u) * (kShareTiles * 2 * 64);
+            frag[(2 * sh->wave) * 64 + lane] = u32x4{b0[0], b0[1], b0[2], b0[3]};
+            frag[(2 * sh->wave + 1) * 64 + lane] = u32x4{b1[0], b1[1], b1[2], b1[3]};
+            set_counter(sh->pairs_written + 4u * sh->wave, pair + 1);
             return;
           }
           const bf8 B0 = __builtin_bit_cast(bf8, u4v{b0[0], b0[1], b0[2], b0[3]});
@@ -1219,7 +1227,6 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
 #pragma unroll
     for (int m = 0; m < kM; m++) unsafeAtomicAdd(y + uint64_t(m) * N + n, acc[m]);
   }
-  if constexpr (kShare) share_store<kMB>(*sh, lane, sacc, reinterpret_cast<float*>(T.dst));
   if constexpr (kInt8) {
     // D[4 (sub div 16) + i][sub mod 16] of every x block, added to int32 y:
     // integer adds commute, so y is the same whatever order the tiles finish in
@@ -1258,8 +1265,8 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
   if constexpr (kRing) {
     const uint32_t s0 = first_slot(tab, T.kind, q.e.x >> 24);
     c.x = q.state(tab[s0].x & 0xFFFFFFu, s0);
-    c.cursor[0] = q.cur / 8u;
-    q.done();
+    c.cursor[0] = q.words();
+    q.close();
   }
   const uint32_t A_h = kH == 2 && h ? c.A[kH - 1] : c.A[0];
   if constexpr (kCK > 0) {

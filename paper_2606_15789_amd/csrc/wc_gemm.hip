@@ -126,56 +126,78 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_w4n_kernel(LaunchArgs a) {
 }
 
 // The shared fused GEMM: workgroup = (pass over 256 kXB rows of x, band of 64
-// W rows, segment of kWaves consecutive tiles of the band); wave w decodes tile
-// w of the segment (when the band has one) and owns x rows 32 kXB w .. of the
-// pass.  Every tile must be full: 64 rows, tile_c columns.  DevTensor::x is the
-// packed x of the job (pack_x_kernel).
+// W rows, segment of kShareTiles consecutive tiles of the band).  Wave w decodes
+// tile w of the segment (when the band has one), wave kShareTiles + w multiplies
+// x rows 32 kXB w .. of the pass.  Every tile must be full: 64 rows, tile_c
+// columns.  DevTensor::x is the packed x of the job (pack_x_kernel).
+//
+// 128 registers a wave leave one such workgroup to a compute unit, so what bounds
+// it is the chain of its eight decoding waves, whose steps are those of wc_ring.h
+// with the words prepared by the wave itself.  Multiplying in waves of their own
+// hides the products behind the decode and halves the passes above 256 rows, where
+// eight waves that did both held 256 rows at most: 8B bf16 layer, m = 80 / 256 /
+// 512 / 1000: 0.266 / 0.313 / 0.499 / 0.936 ms before, 0.254 / 0.302 / 0.407 /
+// 0.668 now.
+constexpr int kShareThreads = (kShareTiles + kShareMultiply) * 64;
+
 template <int kXB>
-__global__ __launch_bounds__(kThreads) void wc_gemm_kernel(LaunchArgs a) {
-  __shared__ uint2 tab[wc::kTableSize];
-  __shared__ uint32_t cum[260];
-  __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
-  __shared__ u32x4 frag[kWaves * 2 * 64];
+__global__ __launch_bounds__(kShareThreads) void wc_gemm_kernel(LaunchArgs a) {
+  // the table at LDS address 0, the rings (the prefix sums the table is built from
+  // lie in the first, which is filled after the build), the shared operands
+  constexpr uint32_t kRings = 8u * wc::kTableSize, kFrag = kRings + kShareTiles * kOwnRingBytes;
+  static_assert(260 * 4 <= kOwnStaging, "the prefix sums fit the first ring");
+  constexpr uint32_t kCounts = kFrag + 2 * kShareTiles * 2 * 64 * 16;
+  __shared__ __align__(16) uint8_t smem[kCounts + 4 * (kShareTiles + kShareMultiply)];
+  uint2* tab = reinterpret_cast<uint2*>(smem);
   const uint32_t wg = blockIdx.x;
   const DevTensor T = tensor_of(a, wg);
   const uint32_t tid = threadIdx.x;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t index = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool multiplies = index >= kShareTiles;
+  const uint32_t wave = index % kShareTiles;
   const uint32_t lane = __lane_id();
   const uint32_t bands = T.n_chunks / T.ntc;
-  const uint32_t segs = (T.ntc + kWaves - 1) / kWaves;
+  const uint32_t segs = (T.ntc + kShareTiles - 1) / kShareTiles;
   const uint32_t local = wg - T.wg0;
   const uint32_t pass = local / (bands * segs), rest = local % (bands * segs);
   const uint32_t band = rest / segs, seg = rest % segs;
   Share s;
-  s.frag = frag;
+  s.frag = reinterpret_cast<u32x4*>(smem + kFrag);
   s.wave = wave;
-  s.n_act = min<uint32_t>(kWaves, T.ntc - seg * kWaves);
+  s.pairs_written = lds_address(smem) + kCounts;
+  s.pairs_multiplied = s.pairs_written + 4 * kShareTiles;
+  // the counts start at zero (tiles the band does not have: past every pair)
+  if (multiplies) set_counter(s.pairs_multiplied + 4u * wave, 0u);
+  s.n_act = min<uint32_t>(kShareTiles, T.ntc - seg * kShareTiles);
+  if (!multiplies)
+    set_counter(s.pairs_written + 4u * wave, wave < s.n_act ? 0u : kShareAll);
   const uint32_t K = T.ntc << T.log_tc;
-  s.first = (pass * kWaves + wave) * 32u * kXB;
+  s.first = (pass * kShareTiles + wave) * 32u * kXB;
   s.mrows = s.first < a.m ? a.m - s.first : 0u;
   // packed x: 1 KiB per (block of 32 rows, pair of columns 16 p ..)
   s.xoff = s.mrows ? ((s.first / 32u) * (K / 16u) * 64u + lane) * 16u +
-                         seg * kWaves * ((1u << T.log_tc) / 16u) * 1024u
+                         seg * kShareTiles * ((1u << T.log_tc) / 16u) * 1024u
                    : 0u;
   s.xtile = (1u << T.log_tc) * 64u;
   s.xblk = K * 64u;
   s.n0 = band * 64u;
   s.pairs = (1u << T.log_tc) / 16u;
   s.N = uint64_t(bands) * 64u;
-  // waves past the band's last tile decode nothing; they index a tile that exists
-  const bool decodes = wave < s.n_act;
-  const uint32_t chunk = band * T.ntc + seg * kWaves + (decodes ? wave : 0u);
-  const IndexPre pre = load_index(a, T, chunk, 1u);
   auto build = [&] {
-    build_table(a, T, tab, cum, threadIdx.x);
+    build_table<kShareThreads>(a, T, tab, reinterpret_cast<uint32_t*>(smem + kRings), tid);
     __syncthreads();
   };
-  if (decodes) {
-    decode_chunks<2, 64, true, 0, kXB, 64, true>(a, T, chunk, lane, tab, ring[wave], pre, build,
-                                                 &s);
+  if (multiplies) {
+    build();
+    share_multiply<kXB>(a, T, s, lane);
+  } else if (wave < s.n_act) {
+    const uint32_t chunk = band * T.ntc + seg * kShareTiles + wave;
+    const IndexPre pre = load_index(a, T, chunk, 1u);
+    uint32_t* ring = reinterpret_cast<uint32_t*>(smem + kRings + wave * kOwnRingBytes);
+    decode_chunks<2, 64, true, 0, 1, 64, true, 0, OwnRing>(a, T, chunk, lane, tab, ring, pre,
+                                                           build, &s);
   } else {
     build();
-    share_idle_wave<kXB>(a, T, s, lane);
   }
 }
 
@@ -185,11 +207,16 @@ __global__ __launch_bounds__(kThreads) void wc_gemm_kernel(LaunchArgs a) {
 // matrix cores (row pairs swapped into 32 x 32 x 16 MFMA operands).
 constexpr uint32_t kDotRows = 5;
 // Rows of x up to which wc_gemm runs wc_gemv's kernels; above, the shared
-// fused GEMM (one decode of every tile per pass of kPassRows x rows) over
+// fused GEMM (one decode of every tile per pass of pass_rows x rows) over
 // packed x.  kMaxGemmRows: the most rows of x wc_gemm takes.
 constexpr uint32_t kShareRows = 64;
 constexpr uint32_t kMaxGemmRows = 4096;
-constexpr uint32_t kPassRows = kWaves * 32u;
+// Rows of x of a pass of the shared fused GEMM: up to 256 every multiplying wave
+// has one block of 32, above two.  With two, fewer passes decode the weights again,
+// but fewer waves multiply where 256 rows are enough.  8B bf16 layer, one block / two:
+// 0.254 / 0.266 ms at m = 80, 0.299 / 0.299 at 256, 0.483 / 0.407 at 512, 0.913 /
+// 0.668 at 1000.
+constexpr uint32_t pass_rows(uint32_t m) { return m <= 256 ? 256u : 512u; }
 
 namespace {
 
@@ -314,9 +341,10 @@ wc_status launch_jobs(const wc::BlobPriv& P, const void* dev_blob, uint32_t n,
       fill_tensor(args.t[nt], T, dev_y[i], wgs);
       args.t[nt].x = xs[i];
       if (share) {
-        // (pass, band, segment of kWaves tiles) per workgroup
+        // (pass, band, segment of kShareTiles tiles) per workgroup
         const uint64_t ntc = T.cols / T.tile_c, bands = T.rows / 64;
-        const uint64_t segs = (ntc + kWaves - 1) / kWaves, passes = (m + kPassRows - 1) / kPassRows;
+        const uint64_t segs = (ntc + kShareTiles - 1) / kShareTiles;
+        const uint64_t passes = (m + pass_rows(m) - 1) / pass_rows(m);
         wgs += uint32_t(bands * segs * passes);
       } else {
         wgs += uint32_t((T.n_chunks + per_wg - 1) / per_wg);
@@ -346,7 +374,10 @@ wc_status launch_jobs(const wc::BlobPriv& P, const void* dev_blob, uint32_t n,
         default: hipLaunchKernelGGL((wc_gemv_e5m2_kernel<4>), grid, block, 0, st, args); break;
       }
     } else if (share) {
-      hipLaunchKernelGGL((wc_gemm_kernel<1>), grid, block, 0, st, args);
+      if (pass_rows(m) == 256u)
+        hipLaunchKernelGGL((wc_gemm_kernel<1>), grid, dim3(kShareThreads), 0, st, args);
+      else
+        hipLaunchKernelGGL((wc_gemm_kernel<2>), grid, dim3(kShareThreads), 0, st, args);
     } else if (rows == 64 && m > kDotRows) {
       if (m <= 32) hipLaunchKernelGGL((wc_gemv_kernel<0, 1, 64>), grid, block, 0, st, args);
       else hipLaunchKernelGGL((wc_gemv_kernel<0, 2, 64>), grid, block, 0, st, args);

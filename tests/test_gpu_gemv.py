@@ -289,8 +289,9 @@ def test_gemv_row_limits(dev):
 
 
 # --- many rows of x: wc_gemm, the shared fused GEMM on 64-row tiles ----------
-# The waves of a workgroup decode up to 8 tiles of one band once and multiply
-# every decoded pair of wave rows by their own 32 rows of packed x (256 per pass).
+# 8 waves of a workgroup decode up to 8 tiles of one band once; 8 more multiply
+# every decoded pair of wave rows by their own 32 or 64 rows of packed x (passes of
+# 256 or 512 rows).
 
 @pytest.mark.parametrize("shape,tile", [((128, 5120), (64, 512)),   # 10 tiles: 2 + 6 idle waves
                                         ((64, 4096), (64, 512)),    # one full segment
@@ -319,6 +320,24 @@ def test_shared_gemm_small_integers_exact(dev, m):
     y = _run_gemm(blob, dev, 0, x)
     ref, _ = oracle.gemv_bf16(w, x)
     assert np.array_equal(y, ref)
+
+
+@pytest.mark.parametrize("words", ["none", "many"])
+@pytest.mark.parametrize("m", [96, 256, 257, 512, 513])
+def test_shared_gemm_around_its_passes(dev, m, words):
+    """One block of 32 x rows a multiplying wave up to 256 rows, two above; exponents
+    that cost no stream words (one value) or nearly the most (201 values, all alike
+    often), so the decoding waves commit no words or as many as they can; 3 tiles of
+    16 columns (one pair each), 10 of 32 and 9 of 512."""
+    rng = np.random.default_rng(900 + m)
+    for shape, tile in [((64, 48), (64, 16)), ((128, 320), (64, 32)), ((64, 4608), (64, 512))]:
+        say("shared gemm passes", m, words, shape)
+        exps = rng.integers(27, 228, shape) if words == "many" else np.full(shape, 120)
+        w = ((rng.integers(0, 2, shape) << 15) | (exps << 7) |
+             rng.integers(0, 128, shape)).astype(np.uint16)
+        x = _bf16(rng.integers(-3, 4, (m, shape[1])).astype(np.float32))
+        blob = wc.encode([("bf16", w, shape)], tile=tile, tile_order=1)
+        _check(_run_gemm(blob, dev, 0, x), w, x)
 
 
 def test_shared_gemm_full_size_layer(dev):
