@@ -422,3 +422,24 @@ def test_device_encoder_rejects_before_any_launch():
                                  C.byref(st)) == -1
     assert lib.wc_analyze_device(odd, C.c_void_p(fake), wc.ANALYZE_WORKSPACE_BYTES, None,
                                  C.byref(st)) == -1
+
+
+@pytest.mark.parametrize("fmt", sorted(wc.DTYPES))
+def test_blob_shapes_and_formats_from_the_descriptors(fmt):
+    """shape and dtype of every tensor of a blob, and none past its bytes or before
+    them."""
+    nbytes = 2 * 64 * 64
+    per = {"bf16": 2, "fp16": 2}.get(fmt)
+    cols = 64 if per else (256 if fmt in ("u4", "fp4_e2m1") else 128)
+    w = np.arange(nbytes, dtype=np.uint32).astype(np.uint8)
+    blob = wc.encode([(fmt, w, (64, cols)), (fmt, w[:0]), (fmt, w)])
+    assert [blob.shape(np.int64(t)) for t in range(3)] == [(64, cols), (0, 0), (0, 0)]
+    assert [blob.dtype(t) for t in range(3)] == [fmt] * 3
+    for t in (-1, 1 << 20):
+        with pytest.raises(IndexError):
+            blob.shape(t)
+        with pytest.raises(IndexError):
+            blob.dtype(t)
+    blob.free()
+    with pytest.raises(ValueError):
+        blob.shape(0)
