@@ -75,6 +75,7 @@ struct EncArgs {
   uint64_t index_off;  // blob offset of the chunk index
   uint64_t raw_start;  // blob offset of the raw regions (after the index)
   uint32_t n_tensors, pad;
+  uint32_t wg0[kMaxLaunch];  // first workgroup of each tensor
   EncTensor t[kMaxLaunch];
 };
 
@@ -152,11 +153,25 @@ __device__ __forceinline__ uint32_t xcd_order(uint32_t b, uint32_t n) {
   return x * q + min(x, r) + k;
 }
 
-__device__ __forceinline__ uint32_t tensor_of(const EncArgs& a, uint32_t wg) {
-  uint32_t ti = 0;
-  for (uint32_t k = 1; k < a.n_tensors; k++)
-    if (wg >= a.t[k].wg0) ti = k;
-  return ti;
+// The tensor of workgroup wg.  Launch arguments lie in host memory, so the first
+// workgroups' time goes to reads that wait for each other: one vector load compares
+// wg with every tensor's first workgroup, and the tensor's fields are then read
+// together.  With norm_kernel's sums by waves instead of one symbol after the other,
+// this took the encode of an 8B bf16 layer (436 MB) from 349 to 338 us.
+__device__ __forceinline__ EncTensor tensor_of(const EncArgs& a, uint32_t wg) {
+  const uint32_t lane = __lane_id();
+  const uint32_t first = a.wg0[lane % kMaxLaunch];
+  const uint64_t before = __ballot(lane < a.n_tensors && first <= wg);
+  const uint32_t ti = __builtin_amdgcn_readfirstlane(__popcll(before) - 1);
+  constexpr int kWords = sizeof(EncTensor) / 4;
+  static_assert(sizeof(EncTensor) % 8 == 0 && kMaxLaunch <= 64);
+  struct Words {
+    uint32_t v[kWords];
+  };
+  Words w = __builtin_bit_cast(Words, a.t[ti]);
+#pragma unroll
+  for (int i = 0; i < kWords; i += 2) asm volatile("" : "+s"(w.v[i]), "+s"(w.v[i + 1]));
+  return __builtin_bit_cast(EncTensor, w);
 }
 
 // ---------------------------------------------------------------------------
@@ -208,7 +223,7 @@ __global__ __launch_bounds__(kHistThreads) void hist_kernel(EncArgs a) {
   __shared__ uint32_t h[256 * 64];
   for (uint32_t i = threadIdx.x; i < 256 * 64; i += kHistThreads) h[i] = 0;
   __syncthreads();
-  const EncTensor& T = a.t[tensor_of(a, blockIdx.x)];
+  const EncTensor T = tensor_of(a, blockIdx.x);
   const uint64_t off0 = uint64_t(blockIdx.x - T.wg0) * kHistSpan;
   const uint64_t off1 = min<uint64_t>(off0 + kHistSpan, T.src_bytes);
   if (T.kind == kSplit16) count_span<kSplit16>(T, off0, off1, h);
@@ -364,21 +379,28 @@ struct NormArgs {
   NormTable t[64];
 };
 
+// Sum of v over the workgroup's 256 threads; part: 4 values in LDS.
+template <class V>
+__device__ __forceinline__ V sum256(V v, V* part) {
+#pragma unroll
+  for (int w = 32; w > 0; w >>= 1) v += __shfl_xor(v, w);
+  if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return part[0] + part[1] + part[2] + part[3];
+}
+
 __global__ __launch_bounds__(256) void norm_kernel(NormArgs a) {
   __shared__ unsigned long long rem[256];
   __shared__ uint32_t cand[256];
   __shared__ uint32_t red[256];
-  __shared__ unsigned long long nsum;
+  __shared__ unsigned long long part[4];
+  __shared__ uint32_t fpart[4], cpart[4];
   const NormTable& NT = a.t[blockIdx.x];
   const uint32_t s = threadIdx.x;
   const unsigned long long* hg =
       reinterpret_cast<const unsigned long long*>(a.ws + a.hist_off) + uint64_t(NT.table) * 256u;
   const unsigned long long c = s < NT.alphabet ? hg[s] : 0ull;
-  if (s == 0) nsum = 0;
-  __syncthreads();
-  atomicAdd(&nsum, c);
-  __syncthreads();
-  const unsigned long long n = nsum;
+  const unsigned long long n = sum256(c, part);
   uint32_t f = 0;
   bool forced = false;
   unsigned long long r = 0;
@@ -393,17 +415,12 @@ __global__ __launch_bounds__(256) void norm_kernel(NormArgs a) {
   }
   rem[s] = r;
   cand[s] = (c && !forced) ? 1u : 0u;
-  red[s] = f;
-  __syncthreads();
-  for (uint32_t w = 128; w > 0; w >>= 1) {
-    if (s < w) red[s] += red[s + w];
-    __syncthreads();
-  }
-  int d = n ? int(wc::kTableSize) - int(red[0]) : 0;
-  __syncthreads();
+  const uint32_t fsum = sum256(f, fpart);  // with a barrier after rem and cand
+  int d = n ? int(wc::kTableSize) - int(fsum) : 0;
   if (d > 0 && cand[s]) {
     // place of this candidate in (remainder descending, symbol ascending)
     uint32_t rank = 0;
+#pragma unroll 16
     for (uint32_t t = 0; t < 256; t++)
       rank += cand[t] && (rem[t] > r || (rem[t] == r && t < s)) ? 1u : 0u;
     if (rank < uint32_t(d)) f += 1;
@@ -422,10 +439,17 @@ __global__ __launch_bounds__(256) void norm_kernel(NormArgs a) {
   }
   // u16 table into the blob; g = 2^12 - f, cum and 1/f for the encoder
   if (s < NT.alphabet) reinterpret_cast<uint16_t*>(a.blob + NT.freq_off)[s] = uint16_t(f);
-  red[s] = f;
+  // cum: the sum of f over the symbols before s, by wave and over the waves
+  uint32_t cum = f;
+#pragma unroll
+  for (uint32_t w = 1; w < 64; w <<= 1) {
+    const uint32_t below = __shfl_up(cum, w);
+    if ((s & 63u) >= w) cum += below;
+  }
+  if ((s & 63u) == 63u) cpart[s >> 6] = cum;
   __syncthreads();
-  uint32_t cum = 0;
-  for (uint32_t t = 0; t < s; t++) cum += red[t];
+  cum -= f;
+  for (uint32_t w = 0; w < s >> 6; w++) cum += cpart[w];
   // 1/f rounded up to a double: the correctly rounded quotient, raised by one
   // unit in the last place when it is below 1/f (the sign of the exact
   // fma(r, f, -1) says which)
@@ -632,7 +656,7 @@ __device__ void encode_chunk(const EncArgs& a, const EncTensor& T, uint32_t c, u
 __global__ __launch_bounds__(kThreads) void encode_kernel(EncArgs a) {
   __shared__ uint4 tab[256];
   const uint32_t wg = xcd_order(blockIdx.x, gridDim.x);
-  const EncTensor& T = a.t[tensor_of(a, wg)];
+  const EncTensor T = tensor_of(a, wg);
   const uint4* tg = reinterpret_cast<const uint4*>(a.ws + a.tab_off) + uint64_t(T.table) * 256u;
   if (threadIdx.x < 256) tab[threadIdx.x] = tg[threadIdx.x];
   __syncthreads();
@@ -777,7 +801,7 @@ __device__ void pack_chunk(const EncArgs& a, const EncTensor& T, uint32_t c, uin
 }
 
 __global__ __launch_bounds__(kThreads) void pack_kernel(EncArgs a) {
-  const EncTensor& T = a.t[tensor_of(a, blockIdx.x)];
+  const EncTensor T = tensor_of(a, blockIdx.x);
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t c = (blockIdx.x - T.wg0) * kWaves + wave;
   if (c >= T.n_chunks) return;
@@ -914,7 +938,7 @@ bool launch_groups(const Plan& P, const wc_dtensor* dt, const WsLayout& L, EncAr
       const uint32_t w = wgs_of(T);
       if (!w) continue;
       fill_enc(args.t[nt], T, dt[t], L, t);
-      args.t[nt].wg0 = wgs;
+      args.t[nt].wg0 = args.wg0[nt] = wgs;
       nt++;
       wgs += w;
     }

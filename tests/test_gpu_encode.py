@@ -437,3 +437,17 @@ def test_word_counts_where_16_bit_counters_overflow(dev, words, kind):
     assert np.array_equal(got["hist"][0], want["hist"][0])
     assert np.array_equal(got["hist"][1], want["hist"][1])
     assert got["H_joint16"] == want["H_joint16"] and got["H"] == want["H"]
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
+@pytest.mark.parametrize("gaps", [False, True])
+def test_tensors_around_a_launchs_limit(dev, n, gaps):
+    """16 tensors to a launch, of one workgroup and of several; with gaps every third,
+    the first too, is empty and takes no workgroup."""
+    rng = np.random.default_rng(n)
+    entries = []
+    for i in range(n):
+        size = 0 if gaps and i % 3 == 0 else [300, 9 * 4096 + 2, 70000][i % 3]
+        entries.append((["bf16", "u8", "u4", "fp8_e4m3"][i % 4],
+                        rng.normal(128, 9, size).astype(np.uint8)))
+    assert_same_blob(entries, dev, chunk_bytes=4096)
