@@ -56,9 +56,9 @@ void wc_decode_kernel(LaunchArgs a) {
 // eight chunks, or two of four, to a compute unit: eight chunks, which is where
 // the kernel ends, since with more the general kernel's 24 waves win (8B int8,
 // 3332 chunks of 1024 steps: 135 us there, 168 to 185 us here).  On a 4 MB
-// bf16 projection (128 chunks of 512 steps) a launch takes 39 us against 56 on
-// the general kernel, on the 8B int4 layer (1760 of 2048 steps) 132 against
-// 184, on 16 ragged fp8 tensors (1340 of 512 steps) 48 against 57.
+// bf16 projection (128 chunks of 512 steps) a call takes 33 us against 51 on
+// the general kernel, on the 8B int4 layer (1760 of 2048 steps) 125 against
+// 187, on 16 ragged fp8 tensors (1340 of 512 steps) 46 against 56.
 template <int kChunks>
 __global__ __launch_bounds__(kChunks * 128) void wc_decode_small_kernel(LaunchArgs a) {
   // the table at LDS address 0 (a slot times 8 is its entry's address), then the
