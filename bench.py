@@ -790,7 +790,8 @@ def gemv_bench(args, dev) -> int:
     stream = torch.cuda.current_stream(dev)
 
     # wc_gemm: wc_gemv up to 64 rows; above, x is packed into the workspace
-    # (inside every timed call) and the weights are decoded once per 256 rows
+    # (inside every timed call) and the weights are decoded once per 256 rows,
+    # once per 512 rows when there are more than 256
     need = wc.gemm_workspace_bytes(blob, list(range(len(W))), [x.data_ptr() for x in xs], M)
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
 

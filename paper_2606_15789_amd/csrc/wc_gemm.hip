@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_w4n_kernel(LaunchArgs a) {
 // with the words prepared by the wave itself.  Multiplying in waves of their own
 // hides the products behind the decode and halves the passes above 256 rows, where
 // eight waves that did both held 256 rows at most: 8B bf16 layer, m = 80 / 256 /
-// 512 / 1000: 0.266 / 0.313 / 0.499 / 0.936 ms before, 0.254 / 0.302 / 0.407 /
+// 512 / 1000: 0.266 / 0.307 / 0.499 / 0.943 ms before, 0.254 / 0.298 / 0.407 /
 // 0.668 now.
 constexpr int kShareThreads = (kShareTiles + kShareMultiply) * 64;
 
