@@ -259,6 +259,8 @@ constexpr uint64_t kSafeWords = 65528;     // below 2^16, whole 16-byte loads
 constexpr uint32_t kWordGroups = 256;      // workgroups: the compute units of an MI355X
 constexpr uint64_t kWordSpan = 64u << 10;  // least source bytes for each
 
+// Bin: the counts' type, 32 bits where they hold all words (analyze_device_into).
+template <class Bin>
 __global__ __launch_bounds__(kWordThreads) void word_hist_kernel(uint64_t src, uint64_t bytes,
                                                                  uint64_t hist, uint64_t span) {
   __shared__ __align__(16) uint32_t c[32768];
@@ -312,7 +314,7 @@ __global__ __launch_bounds__(kWordThreads) void word_hist_kernel(uint64_t src, u
     __syncthreads();
     return r;
   };
-  typedef __attribute__((address_space(1))) unsigned long long gbin;  // no flat access
+  typedef __attribute__((address_space(1))) Bin gbin;  // no flat access
   gbin* g = (gbin*)hist;
   // add the counters to the bins, every workgroup from another bin on
   auto flush = [&] {
@@ -320,10 +322,10 @@ __global__ __launch_bounds__(kWordThreads) void word_hist_kernel(uint64_t src, u
       const uint32_t i = (tid + k + blockIdx.x * (32768u / kWordGroups)) & 32767u;
       const uint32_t v = c[i];
       if (v & 0xFFFFu)
-        __hip_atomic_fetch_add(g + 2 * i, (unsigned long long)(v & 0xFFFFu), __ATOMIC_RELAXED,
+        __hip_atomic_fetch_add(g + 2 * i, Bin(v & 0xFFFFu), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
       if (v >> 16)
-        __hip_atomic_fetch_add(g + 2 * i + 1, (unsigned long long)(v >> 16), __ATOMIC_RELAXED,
+        __hip_atomic_fetch_add(g + 2 * i + 1, Bin(v >> 16), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
@@ -1099,9 +1101,9 @@ extern "C" wc_status wc_encode_device(const wc_dtensor* t, uint32_t n, const wc_
 namespace {
 
 // The histograms of one tensor counted into device memory at dev_workspace
-// (65 536 u64 bins, cleared first by a kernel), copied back into `counts` on
-// the host (as many bins as the format has) and turned into wc_stats.  The
-// caller has checked the arguments.
+// (up to 65 536 u64 bins, cleared first by a kernel), copied back into `counts`
+// on the host (WC_ANALYZE_WORKSPACE_BYTES; as many bins as the format has) and
+// turned into wc_stats.  The caller has checked the arguments.
 wc_status analyze_device_into(const wc_dtensor* t, void* dev_workspace, void* stream,
                               wc_stats* out, uint64_t* counts) {
   const uint32_t dt = uint32_t(t->dtype);
@@ -1109,16 +1111,22 @@ wc_status analyze_device_into(const wc_dtensor* t, void* dev_workspace, void* st
     const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     const uint64_t ws = reinterpret_cast<uint64_t>(dev_workspace);
     const bool words = wc::has_raw(dt);
-    const uint64_t bins = words ? 65536 : 256;
-    hipLaunchKernelGGL(zero_kernel, dim3(uint32_t((bins * 8 / 16 + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<uint4*>(ws), bins * 8 / 16);
+    const uint64_t n_sym = wc::symbols_of(dt, t->nbytes);
+    // Word counts are 32 bits wide while no bin can pass them: copying them back and
+    // walking over them is most of a call beside the kernel (117 MB tensor: 154.7 us a
+    // call with 64-bit counts, 135.3 with these).
+    const bool narrow = words && n_sym <= 0xFFFFFFFFull;
+    const uint64_t bin_bytes = words ? 65536 * (narrow ? 4 : 8) : 256 * 8;
+    hipLaunchKernelGGL(zero_kernel, dim3(uint32_t((bin_bytes / 16 + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<uint4*>(ws), bin_bytes / 16);
     if (hipGetLastError() != hipSuccess) return WC_EHIP;
     if (t->nbytes) {
       if (words) {
         const uint64_t grid = std::min<uint64_t>((t->nbytes + kWordSpan - 1) / kWordSpan,
                                                  kWordGroups);
         const uint64_t span = ((t->nbytes + grid - 1) / grid + 15) / 16 * 16;
-        hipLaunchKernelGGL(word_hist_kernel, dim3(uint32_t(grid)), dim3(kWordThreads), 0, st,
+        hipLaunchKernelGGL(narrow ? word_hist_kernel<uint32_t> : word_hist_kernel<unsigned long long>,
+                           dim3(uint32_t(grid)), dim3(kWordThreads), 0, st,
                            reinterpret_cast<uint64_t>(t->dev_ptr), t->nbytes, ws, span);
         if (hipGetLastError() != hipSuccess) return WC_EHIP;
       } else {
@@ -1137,14 +1145,15 @@ wc_status analyze_device_into(const wc_dtensor* t, void* dev_workspace, void* st
         if (hipGetLastError() != hipSuccess) return WC_EHIP;
       }
     }
-    if (hipMemcpyAsync(counts, dev_workspace, bins * 8, hipMemcpyDeviceToHost, st) != hipSuccess)
+    // narrow counts go to the buffer's upper half, and are widened from its start on
+    uint8_t* to = reinterpret_cast<uint8_t*>(counts) + (narrow ? 65536 * 4 : 0);
+    if (hipMemcpyAsync(to, dev_workspace, bin_bytes, hipMemcpyDeviceToHost, st) != hipSuccess)
       return WC_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return WC_EHIP;
     memset(out, 0, sizeof(*out));
-    const uint64_t n_sym = wc::symbols_of(dt, t->nbytes);
     if (words) {
       // the counts that are not zero, a few thousand of them for weights
-      const uint32_t n = wc::split_word_counts(counts, out);
+      const uint32_t n = wc::split_word_counts(counts, narrow, out);
       wc::finish_stats(dt, n_sym, counts, n, out);
     } else {
       for (uint32_t s = 0; s < 256; s++) out->hist[0][s] = counts[s];

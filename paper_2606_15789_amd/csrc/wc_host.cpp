@@ -274,22 +274,38 @@ void finish_stats(uint32_t dt, uint64_t n, const uint64_t* joint16, uint32_t n_j
   out->H_joint16 = joint16 ? entropy_bits(joint16, n_joint) : NAN;
 }
 
-uint32_t split_word_counts(uint64_t* joint16, wc_stats* out) {
+namespace {
+
+// The words of a count's type, from their place in the buffer to its front.  A
+// group of eight is read before its counts are written, and those of word w end
+// at byte 8 (w + 1) at most: narrow counts not yet read start at 2^18 + 4 (w + 1)
+// or later, which is never below that.
+template <class Count>
+uint32_t split_counts(uint64_t* joint16, wc_stats* out) {
+  const uint8_t* from = reinterpret_cast<const uint8_t*>(joint16) +
+                        65536 * (8 - sizeof(Count));
   uint32_t n = 0;
   for (uint32_t w0 = 0; w0 < 65536; w0 += 8) {
+    Count c[8], any = 0;
+    memcpy(c, from + w0 * sizeof(Count), sizeof c);
+    for (uint32_t k = 0; k < 8; k++) any |= c[k];
     // most words of a tensor of weights never occur: eight at a time
-    uint64_t any = 0;
-    for (uint32_t k = 0; k < 8; k++) any |= joint16[w0 + k];
     if (!any) continue;
-    for (uint32_t w = w0; w < w0 + 8; w++) {
-      const uint64_t c = joint16[w];
-      if (!c) continue;
-      out->hist[0][(w >> 7) & 0xFF] += c;
-      out->hist[1][((w >> 8) & 0x80) | (w & 0x7F)] += c;
-      joint16[n++] = c;
+    for (uint32_t k = 0; k < 8; k++) {
+      if (!c[k]) continue;
+      const uint32_t w = w0 + k;
+      out->hist[0][(w >> 7) & 0xFF] += c[k];
+      out->hist[1][((w >> 8) & 0x80) | (w & 0x7F)] += c[k];
+      joint16[n++] = c[k];
     }
   }
   return n;
+}
+
+}  // namespace
+
+uint32_t split_word_counts(uint64_t* joint16, bool narrow, wc_stats* out) {
+  return narrow ? split_counts<uint32_t>(joint16, out) : split_counts<uint64_t>(joint16, out);
 }
 
 // ---------------------------------------------------------------------------

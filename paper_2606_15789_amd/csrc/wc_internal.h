@@ -144,10 +144,11 @@ inline uint64_t worst_record(const TensorInfo& T, uint64_t n_c) {
 // that are zero left out or not): entropies, bounds, joint entropy.
 void finish_stats(uint32_t dt, uint64_t n, const uint64_t* joint16, uint32_t n_joint,
                   wc_stats* out);
-// Add the 65 536 whole-word counts of a 16-bit format into out->hist[0] (coded
-// field, bits 14..7) and out->hist[1] (raw field, bit 15 and bits 6..0), and move
-// those that are not zero to the front, in order; returns how many.
-uint32_t split_word_counts(uint64_t* joint16, wc_stats* out);
+// Add the 65 536 whole-word counts of a 16-bit format, u64 from joint16 on or
+// (narrow) u32 in the upper half of those 512 KiB, into out->hist[0] (coded field,
+// bits 14..7) and out->hist[1] (raw field, bit 15 and bits 6..0), and move those
+// that are not zero to the front as u64, in order; returns how many.
+uint32_t split_word_counts(uint64_t* joint16, bool narrow, wc_stats* out);
 
 // Validate `size` bytes at `p` and describe them.  Host-side checks of every
 // header field, table sum and index entry; WC_EINVAL on the first failure.

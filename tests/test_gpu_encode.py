@@ -439,6 +439,19 @@ def test_word_counts_where_16_bit_counters_overflow(dev, words, kind):
     assert got["H_joint16"] == want["H_joint16"] and got["H"] == want["H"]
 
 
+@pytest.mark.parametrize("words", [2**32 - 1, 2**32])
+def test_word_counts_where_a_count_leaves_32_bits(dev, words):
+    """A bin holds as many words as the tensor: 32-bit bins up to 2^32 - 1 of them."""
+    say("wide counts", words)
+    x = torch.zeros(words, dtype=torch.int16, device=dev)
+    got = wc.analyze_device("bf16", x.view(torch.uint8))
+    del x
+    torch.cuda.empty_cache()
+    assert [int(h[0]) for h in got["hist"]] == [words] * 2 == [int(h.sum()) for h in got["hist"]]
+    # n * (1 / n), both rounded, is within 2^-53 of 1
+    assert max(abs(h) for h in got["H"] + [got["H_joint16"]]) < 2e-16
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
 @pytest.mark.parametrize("gaps", [False, True])
 def test_tensors_around_a_launchs_limit(dev, n, gaps):
