@@ -452,7 +452,7 @@ def test_word_counts_where_a_count_leaves_32_bits(dev, words):
     assert max(abs(h) for h in got["H"] + [got["H_joint16"]]) < 2e-16
 
 
-@pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 32, 33])
 @pytest.mark.parametrize("gaps", [False, True])
 def test_tensors_around_a_launchs_limit(dev, n, gaps):
     """16 tensors to a launch, of one workgroup and of several; with gaps every third,
