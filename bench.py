@@ -1613,7 +1613,7 @@ def encode_bench(args, dev) -> int:
         "roofline": {"bound": "hbm", "achieved": round(alg / mean_s / 1e9, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(alg / mean_s / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None,
-                     "kernel": "wc_encode_device (7 launches)",
+                     "kernel": "wc_encode_device (6 launches)",
                      "mean_step_us": round(mean_s * 1e6, 2),
                      "algorithmic_bytes_per_step": int(alg)},
         "cpu_baseline": cpu,
