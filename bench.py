@@ -301,17 +301,19 @@ def kernel_fingerprint(name: str = "wc_decode_kernel"):
     return next((v for k, v in prints.items() if name in k), None)
 
 
-def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool) -> str:
+def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool, chunks=None) -> str:
     """The kernel wc_decode runs for one launch of these tensors: its 16-wave
     kernel for bf16/fp16 tensors in untiled 64-lane chunks when the chunks
     exceed the general kernel's resident waves (24 a compute unit: the LDS of
     three 8-wave workgroups) but fit the 16-wave kernel's (32 a compute unit),
-    its kernel for few chunks (up to eight 64-lane chunks a compute unit), the
-    general kernel otherwise.  The library takes the same decision from the
-    runtime's occupancy figures."""
+    its kernel for few chunks (64 lanes; up to four a compute unit, or at most
+    one workgroup of eight), the general kernel otherwise.  `chunks`: those of
+    each tensor (None: all in one).  The library takes the same decision from
+    the runtime's occupancy figures."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    if lanes == 64 and n_chunks <= 8 * cus:
+    if lanes == 64 and (n_chunks <= 4 * cus
+                        or sum(-(-c // 8) for c in chunks or [n_chunks]) <= cus):
         return "wc_decode_small_kernel"
     if (all(d in ("bf16", "fp16") for d in dtypes) and lanes == 64 and not tiled
             and 24 * cus < n_chunks <= 32 * cus):
@@ -711,8 +713,9 @@ def main() -> int:
     else:
         config["copies_resident"] = n_res
         config["step"] = "one wc_decode launch of one resident copy"
+    chunks = None if args.tile else [-(-b // args.chunk_bytes) for b in blobs[0].out_bytes]
     kname = decode_kernel_for([blobs[0].dtype(t) for t in range(blobs[0].n_tensors)],
-                              blobs[0].n_chunks, args.lanes, bool(args.tile))
+                              blobs[0].n_chunks, args.lanes, bool(args.tile), chunks)
     line = {
         "metric": METRIC,
         "value": round(value, 2),
@@ -1711,8 +1714,9 @@ def sweep_bench(args, dev) -> int:
             "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                          "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                          "traffic": None,
-                         "kernel": decode_kernel_for(["bf16"] * len(entries), blob.n_chunks,
-                                                     args.lanes, False),
+                         "kernel": decode_kernel_for(
+                             ["bf16"] * len(entries), blob.n_chunks, args.lanes, False,
+                             [-(-b // args.chunk_bytes) for b in blob.out_bytes]),
                          "mean_launch_us": round(mean_s * 1e6, 2),
                          "algorithmic_bytes_per_launch": int(n + out_b)},
             "compression": {"ratio": round(out_b / n, 5), "bound_ratio": round(out_b / bound, 5),

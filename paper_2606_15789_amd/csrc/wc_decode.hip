@@ -12,10 +12,8 @@
 
 namespace {
 
-// Chunks to a workgroup of the small kernel, at most and in smaller launches.
-// Up to four to a compute unit, workgroups of four have a SIMD for each decoding
-// wave (128 chunks: 42 us, against 45 in workgroups of eight).
-constexpr int kSmallChunks = 8, kFewChunks = 4;
+using wc::kFewChunks;
+using wc::kSmallChunks;
 
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6)))
 void wc_decode_kernel(LaunchArgs a) {
@@ -54,11 +52,14 @@ void wc_decode_kernel(LaunchArgs a) {
 // steps of one LDS round trip, fed by the others (wc_ring.h).  Bound by the
 // chain of a chunk's steps.  Rings of 1024 entries leave LDS for one workgroup of
 // eight chunks, or two of four, to a compute unit: eight chunks, which is where
-// the kernel ends, since with more the general kernel's 24 waves win (8B int8,
-// 3332 chunks of 1024 steps: 135 us there, 168 to 185 us here).  On a 4 MB
-// bf16 projection (128 chunks of 512 steps) a call takes 33 us against 51 on
-// the general kernel, on the 8B int4 layer (1760 of 2048 steps) 125 against
-// 187, on 16 ragged fp8 tensors (1340 of 512 steps) 46 against 56.
+// the kernel ends (wc::DecodeLaunch), since with more the general kernel's 24 waves
+// win (8B int8, 3332 chunks of 1024 steps: 135 us there, 168 to 185 us here).  On an
+// 8 MB bf16 projection (128 chunks of 512 steps) a call takes 36 us against 54 on
+// the general kernel, on the 8B int4 layer (1718 of 2048 steps) 125 against
+// 187, on 16 ragged fp8 tensors (1355 of 512 steps) 46 against 56.  With up to four
+// chunks to a compute unit, workgroups of four have a SIMD for each decoding wave
+// (128 chunks of 64 KiB of another bf16 draw: 42 us, against 45 in workgroups of
+// eight).
 template <int kChunks>
 __global__ __launch_bounds__(kChunks * 128) void wc_decode_small_kernel(LaunchArgs a) {
   // the table at LDS address 0 (a slot times 8 is its entry's address), then the
@@ -105,29 +106,24 @@ __global__ __launch_bounds__(kChunks * 128) void wc_decode_small_kernel(LaunchAr
   }
 }
 
-// Waves of the general kernel and of the 16-bit wide kernel resident on the
-// current device at once, from the runtime's occupancy calculation, and the most
-// chunks of the small kernel's two workgroup sizes, worked out once per device
-// (zeros when unknown: the general kernel is used).
-struct Capacity {
-  uint64_t general, wide, small, few;
-};
-
-Capacity capacity() {
+// The current device's compute units, and the waves of the general kernel and of the
+// 16-bit wide kernel resident on it at once, from the runtime's occupancy calculation,
+// worked out once per device (zeros when unknown: the general kernel is used).
+wc::DecodeCapacity capacity() {
   static std::mutex mu;
-  static std::vector<std::pair<int, Capacity>> known;
+  static std::vector<std::pair<int, wc::DecodeCapacity>> known;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return Capacity{0, 0, 0, 0};
+  if (hipGetDevice(&dev) != hipSuccess) return {0, 0, 0};
   std::lock_guard<std::mutex> lock(mu);
   for (const auto& k : known)
     if (k.first == dev) return k.second;
-  Capacity c{0, 0, 0, 0};
+  wc::DecodeCapacity c{0, 0, 0};
   int cus = 0, per_cu = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
       hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &per_cu, reinterpret_cast<const void*>(wc_decode_kernel), kThreads, 0) == hipSuccess)
-    c = Capacity{uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves), wc::wide_resident_waves(),
-                 uint64_t(cus) * kSmallChunks, uint64_t(cus) * kFewChunks};
+    c = {uint64_t(cus), uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves),
+         wc::wide_resident_waves()};
   known.push_back({dev, c});
   return c;
 }
@@ -160,30 +156,21 @@ extern "C" wc_status wc_decode(const wc_blob* desc, const void* dev_blob, void* 
   while (t < n) {
     // the tensors of one launch: the next kMaxLaunchTensors that have chunks
     uint32_t end = t, nt = 0;
-    uint64_t chunks = 0;
-    bool wide_fits = true, lanes64 = true;
+    wc::DecodeLaunch launch;
     for (; end < n && nt < kMaxLaunchTensors; end++) {
       const wc::TensorInfo& T = P.tensors[end];
       if (T.n_chunks == 0) continue;
       nt++;
-      chunks += T.n_chunks;
-      lanes64 = lanes64 && T.lanes == 64;
-      wide_fits = wide_fits && wc::has_raw(T.dtype) &&
-                  T.lanes == 64 && !T.tile_r;
+      launch.add(T);
     }
     if (nt == 0) break;
-    bool wide = false, small = false, few = false;
-    if (lanes64) {
-      const Capacity cap = capacity();
-      wide = wide_fits && cap.general && cap.wide > cap.general && chunks > cap.general &&
-             chunks <= cap.wide;
-      small = chunks <= cap.small;
-      few = chunks <= cap.few;
-    }
-    const uint64_t waves = wide    ? uint64_t(wc::kWideWaves)
-                           : few   ? uint64_t(kFewChunks)
-                           : small ? uint64_t(kSmallChunks)
-                                   : uint64_t(kWaves);
+    using wc::DecodeKernel;
+    const DecodeKernel kernel =
+        launch.lanes64 ? launch.kernel(capacity()) : DecodeKernel::kGeneral;
+    const uint64_t waves = kernel == DecodeKernel::kWide    ? uint64_t(wc::kWideWaves)
+                           : kernel == DecodeKernel::kFew   ? uint64_t(kFewChunks)
+                           : kernel == DecodeKernel::kSmall ? uint64_t(kSmallChunks)
+                                                            : uint64_t(kWaves);
     uint32_t wgs = 0;
     nt = 0;
     for (; t < end; t++) {
@@ -194,20 +181,24 @@ extern "C" wc_status wc_decode(const wc_blob* desc, const void* dev_blob, void* 
       wgs += (uint32_t)((T.n_chunks + per_group - 1) / per_group);
     }
     set_tensors(args, nt);
-    if (wide) {
-      if (!wc::wide_launch(&args, sizeof args, wgs, stream)) return WC_EHIP;
-    } else {
-      const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-      if (few)
+    const hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    switch (kernel) {
+      case DecodeKernel::kWide:
+        if (!wc::wide_launch(&args, sizeof args, wgs, stream)) return WC_EHIP;
+        continue;
+      case DecodeKernel::kFew:
         hipLaunchKernelGGL(wc_decode_small_kernel<kFewChunks>, dim3(wgs), dim3(kFewChunks * 128), 0,
                            st, args);
-      else if (small)
+        break;
+      case DecodeKernel::kSmall:
         hipLaunchKernelGGL(wc_decode_small_kernel<kSmallChunks>, dim3(wgs),
                            dim3(kSmallChunks * 128), 0, st, args);
-      else
+        break;
+      case DecodeKernel::kGeneral:
         hipLaunchKernelGGL(wc_decode_kernel, dim3(wgs), dim3(kThreads), 0, st, args);
-      if (hipGetLastError() != hipSuccess) return WC_EHIP;
+        break;
     }
+    if (hipGetLastError() != hipSuccess) return WC_EHIP;
   }
   return WC_OK;
 }

@@ -101,6 +101,45 @@ struct BlobPriv {
   uint64_t n_chunks = 0, index_off = 0, raw_off = 0, records_off = 0, size = 0;
 };
 
+// Which kernel decodes a launch (wc_decode.hip), from what its tensors add up to
+// and the device's compute units and resident waves.
+//
+// The small kernel is for launches whose workgroups all run at once, one of eight
+// chunks to a compute unit: what counts is its workgroups, not its chunks, because
+// every tensor's last one may be short.  30 tensors of 65 chunks (1950 chunks in 270
+// workgroups, 256 compute units) take 127 us on the general kernel and 161 in two
+// rounds of small workgroups (64 KiB int8 chunks; bf16 74 and 77, int4 234 and 242).
+// With up to four chunks to a compute unit its workgroups are of four: two fit a
+// compute unit, so 32 short ones more are no second round.
+constexpr uint32_t kSmallChunks = 8, kFewChunks = 4;
+
+enum class DecodeKernel { kGeneral, kWide, kSmall, kFew };
+
+struct DecodeCapacity {
+  uint64_t cus, general, wide;  // compute units; resident waves of two kernels
+};
+
+struct DecodeLaunch {
+  uint64_t chunks = 0, small_wgs = 0;
+  bool lanes64 = true, wide_fits = true;
+
+  void add(const TensorInfo& T) {
+    chunks += T.n_chunks;
+    small_wgs += (T.n_chunks + kSmallChunks - 1) / kSmallChunks;
+    lanes64 = lanes64 && T.lanes == 64;
+    wide_fits = wide_fits && has_raw(T.dtype) && T.lanes == 64 && !T.tile_r;
+  }
+  DecodeKernel kernel(const DecodeCapacity& cap) const {
+    if (!lanes64) return DecodeKernel::kGeneral;
+    if (wide_fits && cap.general && cap.wide > cap.general && chunks > cap.general &&
+        chunks <= cap.wide)
+      return DecodeKernel::kWide;
+    if (chunks <= cap.cus * kFewChunks) return DecodeKernel::kFew;
+    if (small_wgs <= cap.cus) return DecodeKernel::kSmall;
+    return DecodeKernel::kGeneral;
+  }
+};
+
 // What a wc_blob's `priv` points at: the public struct and the parsed blob.
 struct BlobHandle {
   wc_blob pub;

@@ -49,6 +49,14 @@ def test_decode_kernel_window_needs_untiled_16_bit_64_lane_launches(bench, cus_2
     assert bench.decode_kernel_for(["bf16", "u8"], 7000, 64, False) == "wc_decode_kernel"
 
 
+def test_decode_kernel_for_few_chunks(bench, cus_256):
+    name = lambda chunks: bench.decode_kernel_for(  # noqa: E731
+        ["u4"] * len(chunks), sum(chunks), 64, False, chunks)
+    assert name([1]) == name([2048]) == name([64] * 32) == "wc_decode_small_kernel"
+    assert name([2049]) == name([65] * 30) == "wc_decode_kernel"
+    assert bench.decode_kernel_for(["u4"], 1, 32, False) == "wc_decode_kernel"
+
+
 @pytest.mark.parametrize("weights,rows", [("bf16", 16), ("int8", 16), ("e4m3", 16), ("e5m2", 16),
                                           ("mxfp4-bytes", 8), ("int4-bytes", 8)])
 def test_gemv_kernel_window(bench, cus_256, weights, rows):

@@ -1,0 +1,87 @@
+"""CPU checks of the rule by which wc_decode picks a launch's kernel
+(DecodeLaunch in csrc/wc_internal.h), compiled on its own with the host
+compiler, for a device of 256 compute units that holds 24 waves a unit of the
+general kernel and 32 of the 16-wave one."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+DTYPES = {"bf16": (1, 2), "u8": (3, 1), "u4": (4, 1), "fp8_e4m3": (5, 1)}
+CUS = 256
+
+DRIVER = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "wc_internal.h"
+// argv: cus, then dtype, decoded bytes, chunk bytes, lanes, tiled of every tensor
+int main(int argc, char** argv) {
+  const uint64_t cus = strtoull(argv[1], nullptr, 10);
+  wc::DecodeLaunch launch;
+  for (int i = 2; i + 4 < argc; i += 5) {
+    wc::TensorInfo T;
+    T.dtype = uint32_t(atoi(argv[i]));
+    T.out_bytes = strtoull(argv[i + 1], nullptr, 10);
+    T.chunk_bytes = uint32_t(atoi(argv[i + 2]));
+    T.lanes = uint32_t(atoi(argv[i + 3]));
+    T.tile_r = uint32_t(atoi(argv[i + 4]));
+    T.n_sym = wc::symbols_of(T.dtype, T.out_bytes);
+    T.n_chunks = (T.out_bytes + T.chunk_bytes - 1) / T.chunk_bytes;
+    launch.add(T);
+  }
+  const char* names[] = {"general", "wide", "small", "few"};
+  puts(names[int(launch.kernel({cus, cus * 24, cus * 32}))]);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no host C++ compiler")
+    d = tmp_path_factory.mktemp("rule")
+    src, exe = d / "rule.cpp", d / "rule"
+    src.write_text(DRIVER)
+    subprocess.run([gxx, "-std=c++20", "-O1", "-Wall", "-Werror",
+                    "-I" + os.path.join(ROOT, "paper_2606_15789_amd", "csrc"), str(src),
+                    "-o", str(exe)], check=True, capture_output=True, text=True)
+
+    def kernel(tensors, cus=CUS, chunk_bytes=65536, lanes=64, tiled=False):
+        """tensors: (dtype, chunks) pairs."""
+        args = [str(cus)]
+        for dt, chunks in tensors:
+            args += [str(DTYPES[dt][0]), str(int(chunks * chunk_bytes)), str(chunk_bytes),
+                     str(lanes), str(int(tiled))]
+        return subprocess.run([str(exe), *args], check=True, capture_output=True,
+                              text=True).stdout.strip()
+
+    return kernel
+
+
+def test_windows_of_one_tensor(rule):
+    assert rule([("bf16", 1)]) == "few"
+    assert rule([("bf16", 4 * CUS)]) == "few"
+    assert rule([("u4", 4 * CUS + 1)]) == "small"
+    assert rule([("u4", 8 * CUS)]) == "small"
+    assert rule([("u4", 8 * CUS + 1)]) == "general"
+    assert rule([("bf16", 24 * CUS)]) == "general"
+    assert rule([("bf16", 24 * CUS + 1)]) == "wide"
+    assert rule([("bf16", 32 * CUS)]) == "wide"
+    assert rule([("bf16", 32 * CUS + 1)]) == "general"
+    assert rule([("bf16", 24 * CUS + 1)], tiled=True) == "general"
+    assert rule([("u8", 24 * CUS + 1)]) == "general"
+    assert rule([("u8", 1)], lanes=32) == "general"
+    assert rule([("u8", 1)], cus=0) == "general"
+
+
+def test_small_workgroups_beyond_the_compute_units_are_no_second_round(rule):
+    """Short last workgroups count: 30 tensors of 65 chunks are 270 workgroups of
+    eight."""
+    assert rule([("u4", 65)] * 30) == "general"
+    assert rule([("u4", 64)] * 32) == "small"
+    assert rule([("u4", 2017)] + [("u4", 1)] * 31) == "general"
+    assert rule([("u4", 1961)] + [("u4", 1)] * 10) == "small"  # 246 + 10 workgroups
+    assert rule([("u4", 1961)] + [("u4", 1)] * 11) == "general"
