@@ -301,19 +301,24 @@ def kernel_fingerprint(name: str = "wc_decode_kernel"):
     return next((v for k, v in prints.items() if name in k), None)
 
 
-def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool, chunks=None) -> str:
+def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool, out_bytes=None,
+                      chunk_bytes: int = 65536) -> str:
     """The kernel wc_decode runs for one launch of these tensors: its 16-wave
     kernel for bf16/fp16 tensors in untiled 64-lane chunks when the chunks
     exceed the general kernel's resident waves (24 a compute unit: the LDS of
     three 8-wave workgroups) but fit the 16-wave kernel's (32 a compute unit),
     its kernel for few chunks (64 lanes; up to four a compute unit, or at most
-    one workgroup of eight), the general kernel otherwise.  `chunks`: those of
-    each tensor (None: all in one).  The library takes the same decision from
-    the runtime's occupancy figures."""
+    one workgroup of eight; 32 steps of 64 symbols in the longest), the general
+    kernel otherwise.  `out_bytes`: the decoded bytes of each tensor (None: the
+    chunks are one tensor's and full).  The library takes the same decision
+    from the runtime's occupancy figures."""
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    if lanes == 64 and (n_chunks <= 4 * cus
-                        or sum(-(-c // 8) for c in chunks or [n_chunks]) <= cus):
+    sizes = list(zip(dtypes, out_bytes)) if out_bytes else [(dtypes[0], n_chunks * chunk_bytes)]
+    per_byte = {"bf16": 0.5, "fp16": 0.5, "u4": 2, "fp4_e2m1": 2}
+    steps = max(min(b, chunk_bytes) * per_byte.get(d, 1) / 64 for d, b in sizes)
+    workgroups = sum(-(-b // (8 * chunk_bytes)) for _, b in sizes)
+    if lanes == 64 and steps > 31 and (n_chunks <= 4 * cus or workgroups <= cus):
         return "wc_decode_small_kernel"
     if (all(d in ("bf16", "fp16") for d in dtypes) and lanes == 64 and not tiled
             and 24 * cus < n_chunks <= 32 * cus):
@@ -713,9 +718,9 @@ def main() -> int:
     else:
         config["copies_resident"] = n_res
         config["step"] = "one wc_decode launch of one resident copy"
-    chunks = None if args.tile else [-(-b // args.chunk_bytes) for b in blobs[0].out_bytes]
     kname = decode_kernel_for([blobs[0].dtype(t) for t in range(blobs[0].n_tensors)],
-                              blobs[0].n_chunks, args.lanes, bool(args.tile), chunks)
+                              blobs[0].n_chunks, args.lanes, bool(args.tile),
+                              None if args.tile else blobs[0].out_bytes, args.chunk_bytes)
     line = {
         "metric": METRIC,
         "value": round(value, 2),
@@ -1716,7 +1721,7 @@ def sweep_bench(args, dev) -> int:
                          "traffic": None,
                          "kernel": decode_kernel_for(
                              ["bf16"] * len(entries), blob.n_chunks, args.lanes, False,
-                             [-(-b // args.chunk_bytes) for b in blob.out_bytes]),
+                             blob.out_bytes, args.chunk_bytes),
                          "mean_launch_us": round(mean_s * 1e6, 2),
                          "algorithmic_bytes_per_launch": int(n + out_b)},
             "compression": {"ratio": round(out_b / n, 5), "bound_ratio": round(out_b / bound, 5),

@@ -50,11 +50,13 @@ def test_decode_kernel_window_needs_untiled_16_bit_64_lane_launches(bench, cus_2
 
 
 def test_decode_kernel_for_few_chunks(bench, cus_256):
-    name = lambda chunks: bench.decode_kernel_for(  # noqa: E731
-        ["u4"] * len(chunks), sum(chunks), 64, False, chunks)
+    name = lambda chunks, cb=65536: bench.decode_kernel_for(  # noqa: E731
+        ["u4"] * len(chunks), sum(chunks), 64, False, [c * cb for c in chunks], cb)
     assert name([1]) == name([2048]) == name([64] * 32) == "wc_decode_small_kernel"
     assert name([2049]) == name([65] * 30) == "wc_decode_kernel"
+    assert name([1], 1024) == "wc_decode_small_kernel" and name([1], 512) == "wc_decode_kernel"
     assert bench.decode_kernel_for(["u4"], 1, 32, False) == "wc_decode_kernel"
+    assert bench.decode_kernel_for(["u4"], 1, 64, True) == "wc_decode_small_kernel"
 
 
 @pytest.mark.parametrize("weights,rows", [("bf16", 16), ("int8", 16), ("e4m3", 16), ("e5m2", 16),

@@ -85,3 +85,15 @@ def test_small_workgroups_beyond_the_compute_units_are_no_second_round(rule):
     assert rule([("u4", 2017)] + [("u4", 1)] * 31) == "general"
     assert rule([("u4", 1961)] + [("u4", 1)] * 10) == "small"  # 246 + 10 workgroups
     assert rule([("u4", 1961)] + [("u4", 1)] * 11) == "general"
+
+
+def test_short_chunks_take_the_general_kernel(rule):
+    """A launch whose longest chunk has fewer than 32 steps (2048 symbols)."""
+    for dtype, nbytes in [("bf16", 4096), ("u8", 2048), ("u4", 1024)]:
+        for n, chunks in [("few", 1000), ("small", 2000)]:
+            assert rule([(dtype, chunks)], chunk_bytes=nbytes) == n
+            assert rule([(dtype, chunks)], chunk_bytes=nbytes // 2) == "general"
+    # one chunk that its tensor does not fill
+    assert rule([("u8", 2048 / 65536)]) == "few"
+    assert rule([("u8", 1984 / 65536)]) == "general"
+    assert rule([("u8", 1 / 65536), ("bf16", 1)]) == "few"  # the longest counts
