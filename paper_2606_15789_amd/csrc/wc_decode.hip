@@ -15,13 +15,14 @@ namespace {
 using wc::kFewChunks;
 using wc::kSmallChunks;
 
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6)))
-void wc_decode_kernel(LaunchArgs a) {
+__global__ __launch_bounds__(kThreads) void wc_decode_kernel(LaunchArgs a) {
   __shared__ uint2 tab[wc::kTableSize];
   __shared__ uint32_t cum[260];
   __shared__ uint32_t ring[kWaves][wc_ring_words() / 2];
   const uint32_t wg = xcd_order(blockIdx.x, gridDim.x);
-  const DevTensor T = tensor_of<false>(a, wg);  // its registers have no room for all fields
+  // read where they are used: held together across twelve decoders, the fields
+  // spilled 14 scalar registers
+  const DevTensor& T = a.t[tensor_index(a, wg)];
   const WaveOf w = wave_of(a, T, wg, kWaves, T.lanes == 32 ? 2u : 1u);
   auto build = [&] {
     build_table(a, T, tab, cum, threadIdx.x);

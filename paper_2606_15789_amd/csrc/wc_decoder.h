@@ -311,25 +311,25 @@ __device__ __forceinline__ IndexPre load_index(const LaunchArgs& a, const DevTen
 // The tensor of workgroup wg.  A launch's first look at its arguments goes to
 // host memory, so what matters is how many such reads wait for each other (a
 // launch of 2048 chunks of 32 steps: 19 us when they did, 10 us): one vector
-// load compares wg with every tensor's first workgroup at once, and the
-// tensor's fields then arrive together (kTogether), not one by one where they are
-// used.
-template <bool kTogether = true>
-__device__ __forceinline__ DevTensor tensor_of(const LaunchArgs& a, uint32_t wg) {
+// load compares wg with every tensor's first workgroup at once (tensor_index), and
+// the tensor's fields then arrive together, not one by one where they are used
+// (tensor_of).
+__device__ __forceinline__ uint32_t tensor_index(const LaunchArgs& a, uint32_t wg) {
   const uint32_t lane = __lane_id();
   const uint32_t first = a.wg0[lane % kMaxLaunchTensors];
   const uint32_t before = (uint32_t)__ballot(lane < kMaxLaunchTensors && first <= wg);
-  const uint32_t ti = __builtin_amdgcn_readfirstlane(__popc(before) - 1);
+  return __builtin_amdgcn_readfirstlane(__popc(before) - 1);
+}
+
+__device__ __forceinline__ DevTensor tensor_of(const LaunchArgs& a, uint32_t wg) {
   constexpr int kWords = sizeof(DevTensor) / 4;
   static_assert(sizeof(DevTensor) % 8 == 0 && kWords <= 32, "loaded as scalar registers");
   struct Words {
     uint32_t v[kWords];
   };
-  Words w = __builtin_bit_cast(Words, a.t[ti]);
-  if constexpr (kTogether) {
+  Words w = __builtin_bit_cast(Words, a.t[tensor_index(a, wg)]);
 #pragma unroll
-    for (int i = 0; i < kWords; i += 2) asm volatile("" : "+s"(w.v[i]), "+s"(w.v[i + 1]));
-  }
+  for (int i = 0; i < kWords; i += 2) asm volatile("" : "+s"(w.v[i]), "+s"(w.v[i + 1]));
   return __builtin_bit_cast(DevTensor, w);
 }
 
@@ -985,6 +985,10 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
         raw2 = d & 1 ? src >> 16 : src;
       }
       ow[d] = assemble<G>(lo, raw2);
+      // assembled here: the entries of 32 steps kept for the end of a nibble row were
+      // 26 registers of wc_decode_kernel (80 and a spill, 54 without); the kernel for
+      // few chunks has registers for them, and its bf16 decode is 2 % slower with this
+      if constexpr (G == 8 && !kMfma && !kRing) asm volatile("" : "+v"(ow[d]));
       if constexpr (kCK > 0 && d == 0) {
         if (kFirst || (kTail && r == 0)) first_dw = ow[0];
       }
