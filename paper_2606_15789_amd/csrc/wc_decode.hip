@@ -3,11 +3,6 @@
 // The general kernel and the one for few chunks are here; bf16/fp16 launches
 // that just overflow the general kernel's resident waves run on the 16-wave
 // kernel of wc_decode_wide.hip.
-
-#include <mutex>
-#include <utility>
-#include <vector>
-
 #include "wc_decoder.h"
 
 namespace {
@@ -111,22 +106,18 @@ __global__ __launch_bounds__(kChunks * 128) void wc_decode_small_kernel(LaunchAr
 // 16-bit wide kernel resident on it at once, from the runtime's occupancy calculation,
 // worked out once per device (zeros when unknown: the general kernel is used).
 wc::DecodeCapacity capacity() {
-  static std::mutex mu;
-  static std::vector<std::pair<int, wc::DecodeCapacity>> known;
+  static wc::PerDevice<wc::DecodeCapacity> known;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return {0, 0, 0};
-  std::lock_guard<std::mutex> lock(mu);
-  for (const auto& k : known)
-    if (k.first == dev) return k.second;
-  wc::DecodeCapacity c{0, 0, 0};
-  int cus = 0, per_cu = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &per_cu, reinterpret_cast<const void*>(wc_decode_kernel), kThreads, 0) == hipSuccess)
-    c = {uint64_t(cus), uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves),
-         wc::wide_resident_waves()};
-  known.push_back({dev, c});
-  return c;
+  return known.get(dev, [&]() -> wc::DecodeCapacity {
+    int cus = 0, per_cu = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &per_cu, reinterpret_cast<const void*>(wc_decode_kernel), kThreads, 0) != hipSuccess)
+      return {0, 0, 0};
+    return {uint64_t(cus), uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves),
+            wc::wide_resident_waves()};
+  });
 }
 
 // A tiled tensor whose widest output descriptor (two tiles of a 32-lane wave)

@@ -1,11 +1,6 @@
 // wc_gemm.hip -- the fused decode-GEMMs (Alg. 1 / 3): wc_gemv, wc_gemm,
 // wc_gemm_workspace_bytes, wc_gemm_i8.  The weights are decoded by the
 // decoder of wc_decoder.h and multiplied on chip, never written to memory.
-
-#include <mutex>
-#include <utility>
-#include <vector>
-
 #include "wc_decoder.h"
 
 namespace {
@@ -270,32 +265,24 @@ bool gemv_wide(int kind, uint64_t tiles) {
     uint64_t general, wide;
   };
   if (kind < 0 || kind > 5) return false;
-  static std::mutex mu;
-  static std::vector<std::pair<int, Cap>> known[6];
+  static wc::PerDevice<Cap> known[6];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
-  Cap c{0, 0};
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    bool found = false;
-    for (const auto& k : known[kind])
-      if (k.first == dev) c = k.second, found = true;
-    if (!found) {
-      int cus = 0, per_cu = 0;
-      const void* k8 =
-          kind == 5   ? reinterpret_cast<const void*>(wc_gemv_kernel<0, 1, 16>)
-          : kind == 4 ? reinterpret_cast<const void*>(wc_gemv_w4_kernel<1>)
-          : kind == 3 ? reinterpret_cast<const void*>(wc_gemv_mxb_kernel<1>)
-          : kind == 2 ? reinterpret_cast<const void*>(wc_gemv_e5m2_kernel<1>)
-          : kind == 1 ? reinterpret_cast<const void*>(wc_gemv_kernel<0, 1, 16, 4, true>)
-                      : reinterpret_cast<const void*>(wc_gemv_kernel<0, 1, 16, 4, false>);
-      if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k8, kThreads, 0) == hipSuccess)
-        c = Cap{uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves),
-                wc::gemv_wide_resident_waves(kind)};
-      known[kind].push_back({dev, c});
-    }
-  }
+  const Cap c = known[kind].get(dev, [&]() -> Cap {
+    int cus = 0, per_cu = 0;
+    const void* k8 =
+        kind == 5   ? reinterpret_cast<const void*>(wc_gemv_kernel<0, 1, 16>)
+        : kind == 4 ? reinterpret_cast<const void*>(wc_gemv_w4_kernel<1>)
+        : kind == 3 ? reinterpret_cast<const void*>(wc_gemv_mxb_kernel<1>)
+        : kind == 2 ? reinterpret_cast<const void*>(wc_gemv_e5m2_kernel<1>)
+        : kind == 1 ? reinterpret_cast<const void*>(wc_gemv_kernel<0, 1, 16, 4, true>)
+                    : reinterpret_cast<const void*>(wc_gemv_kernel<0, 1, 16, 4, false>);
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k8, kThreads, 0) != hipSuccess)
+      return {0, 0};
+    return {uint64_t(cus) * uint64_t(per_cu) * uint64_t(kWaves),
+            wc::gemv_wide_resident_waves(kind)};
+  });
   return c.general && c.wide > c.general && tiles > c.general && tiles <= c.wide;
 }
 

@@ -4,6 +4,7 @@
 
 #include <stdint.h>
 
+#include <mutex>
 #include <vector>
 
 #include "../../include/wc.h"
@@ -146,6 +147,30 @@ struct DecodeLaunch {
     if (small_wgs <= cap.cus) return DecodeKernel::kSmall;
     return DecodeKernel::kGeneral;
   }
+};
+
+// A value per device, worked out at its first use and kept without an allocation: an
+// entry point that promises none, and that no C++ exception may leave, asks for it.
+// Past kDevices devices it is worked out on every call.
+template <class V>
+class PerDevice {
+ public:
+  template <class Make>
+  V get(int dev, Make make) {
+    if (dev < 0 || dev >= kDevices) return make();
+    std::lock_guard<std::mutex> lock(mu_);
+    if (!known_[dev]) {
+      value_[dev] = make();
+      known_[dev] = true;
+    }
+    return value_[dev];
+  }
+
+ private:
+  static constexpr int kDevices = 64;
+  std::mutex mu_;
+  bool known_[kDevices] = {};
+  V value_[kDevices] = {};
 };
 
 // What a wc_blob's `priv` points at: the public struct and the parsed blob.

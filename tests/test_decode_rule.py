@@ -97,3 +97,51 @@ def test_short_chunks_take_the_general_kernel(rule):
     assert rule([("u8", 2048 / 65536)]) == "few"
     assert rule([("u8", 1984 / 65536)]) == "general"
     assert rule([("u8", 1 / 65536), ("bf16", 1)]) == "few"  # the longest counts
+
+
+NO_ALLOCATION = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <new>
+#include "wc_internal.h"
+static bool full = false;  // memory has run out
+void* operator new(size_t n) {
+  void* p = full ? nullptr : malloc(n);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+int main() {
+  static wc::PerDevice<wc::DecodeCapacity> known;
+  full = true;
+  int made = 0;
+  for (int pass = 0; pass < 2; pass++)
+    for (int dev = 0; dev < 64; dev++)
+      if (known.get(dev, [&]() -> wc::DecodeCapacity {
+                made++;
+                return {uint64_t(dev), 1, 2};
+              }).cus != uint64_t(dev))
+        return 1;
+  if (made != 64) return 2;
+  // devices past the table, or none: worked out each time
+  for (int dev : {64, 1000, -1})
+    if (known.get(dev, [&]() -> wc::DecodeCapacity { return {7, 1, 2}; }).cus != 7) return 3;
+  return 0;
+}
+"""
+
+
+def test_device_figures_are_kept_without_an_allocation(tmp_path):
+    """wc_decode asks for the device's figures on every launch of 64-lane chunks
+    and promises its caller no allocation: none where memory has run out, and so
+    no exception out of a C entry."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no host C++ compiler")
+    src, exe = tmp_path / "a.cpp", tmp_path / "a"
+    src.write_text(NO_ALLOCATION)
+    subprocess.run([gxx, "-std=c++20", "-O1", "-Wall", "-Werror", "-pthread",
+                    "-I" + os.path.join(ROOT, "paper_2606_15789_amd", "csrc"), str(src),
+                    "-o", str(exe)], check=True, capture_output=True, text=True)
+    assert subprocess.run([str(exe)]).returncode == 0
