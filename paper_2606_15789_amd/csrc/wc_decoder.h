@@ -574,10 +574,10 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 // The first kShareTiles waves of a workgroup decode that many consecutive tiles of
 // one band of 64 W rows (one tile each); the other waves multiply.  After each
 // pair of wave rows a decoding wave leaves its two v_mfma_f32_32x32x16_bf16 B
-// operands (64 W rows x 16 columns) in one half of an LDS buffer, and while the
-// next pair is decoded into the other half, every multiplying wave takes all of
-// them times its own kXB blocks of 32 x rows, so that the matrix cores work beside
-// the decode.  Each wave publishes how many pairs it has written or multiplied,
+// operands (64 W rows x 16 columns) in LDS, and while the next pair is decoded, every
+// multiplying wave takes all of them times its own kXB blocks of 32 x rows, so that
+// the matrix cores work beside the decode.  With two LDS buffers the next pair goes to
+// the other one; with one it waits in registers until the last is multiplied.  Each wave publishes how many pairs it has written or multiplied,
 // and the waves wait for each other's counts, not for all waves at a barrier: a
 // decoding wave that commits words (wc_ring.h) in one pair may catch up in the next
 // (2 % on the 8B layer at m = 80).  The waits end: the pair a wave waits for never
@@ -586,7 +586,7 @@ constexpr int kShareTiles = 8;
 constexpr int kShareMultiply = 8;  // multiplying waves
 constexpr uint32_t kShareAll = 0x7FFFFFFFu;
 struct Share {
-  u32x4* frag;     // LDS [2][kShareTiles][2][64]: the tiles' B operands of two pairs
+  u32x4* frag;     // LDS [buffers][kShareTiles][2][64]: the tiles' B operands of a pair
   uint32_t pairs_written;     // LDS address of [kShareTiles] counts: pairs of each tile written
   uint32_t pairs_multiplied;  // and of [kShareMultiply]: pairs each multiplying wave is past
   uint32_t wave;   // decoding: this wave's tile; multiplying: its blocks of x rows
@@ -644,14 +644,14 @@ __device__ __forceinline__ void share_store(const Share& s, uint32_t lane,
 
 // A multiplying wave: acc[xb][nb] += x block xb times W rows 32 nb .. 32 nb + 31 of
 // every tile, pair after pair.  x is loaded kAhead tiles ahead, across the pairs.
-template <int kXB>
+template <int kXB, int kBuffers, int kAhead>
 __device__ __forceinline__ void share_multiply(const LaunchArgs& a, const DevTensor& T,
                                                const Share& s, uint32_t lane) {
   if (s.mrows == 0) {  // no rows of x in this pass
     set_counter(s.pairs_multiplied + 4u * s.wave, kShareAll);
     return;
   }
-  constexpr int kAhead = 4;
+  static_assert(kBuffers == 1 || kBuffers == 2);
   static_assert(kShareTiles % kAhead == 0, "a tile's place in x is known at compile time");
   const uint32_t K = T.ntc << T.log_tc;
   const __amdgpu_buffer_rsrc_t xrs =
@@ -664,7 +664,7 @@ __device__ __forceinline__ void share_multiply(const LaunchArgs& a, const DevTen
   for (int f = 0; f < kAhead; f++) share_load_x<kXB>(s, xrs, f, 0, x[f]);
   for (uint32_t p = 0; p < s.pairs; p++) {
     share_wait(s.pairs_written, kShareTiles, p + 1);
-    const u32x4* frag = s.frag + (p & 1u) * (kShareTiles * 2 * 64);
+    const u32x4* frag = s.frag + (p & (kBuffers - 1u)) * (kShareTiles * 2 * 64);
 #pragma unroll
     for (int f = 0; f < kShareTiles; f++) {
       if (uint32_t(f) < s.n_act) {
@@ -719,10 +719,10 @@ __device__ __forceinline__ void share_multiply(const LaunchArgs& a, const DevTen
 // keep row r, lanes 32..63 take row r + 1 of the same W rows), which share
 // one A operand of x, so every x value loaded feeds 64 W rows.
 //
-// kShare (with kMR = 64): a decoding wave of the shared fused GEMM.  The two B
-// operands of each pair go to this wave's slot in LDS, for the multiplying waves
-// (see Share).
-template <int G, int L, bool kTiled, int kM = 0, int kMB = 0, int kMR = 16, bool kShare = false,
+// kShare (with kMR = 64): a decoding wave of the shared fused GEMM, with kShare LDS
+// buffers.  The two B operands of each pair go to this wave's slot in one of them,
+// for the multiplying waves (see Share).
+template <int G, int L, bool kTiled, int kM = 0, int kMB = 0, int kMR = 16, int kShare = 0,
           int kWF = 0, class RingOf = void, class Build>
 __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTensor& T,
                                               uint32_t chunk_of_wave, uint32_t lane,
@@ -985,10 +985,13 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
         raw2 = d & 1 ? src >> 16 : src;
       }
       ow[d] = assemble<G>(lo, raw2);
-      // assembled here: the entries of 32 steps kept for the end of a nibble row were
-      // 26 registers of wc_decode_kernel (80 and a spill, 54 without); the kernel for
-      // few chunks has registers for them, and its bf16 decode is 2 % slower with this
-      if constexpr (G == 8 && !kMfma && !kRing) asm volatile("" : "+v"(ow[d]));
+      // assembled here, where registers are short: the entries of 32 steps kept for the
+      // end of a nibble row were 26 registers of wc_decode_kernel (80 and a spill, 54
+      // without), those of a pair of rows 17 spilled ones of the shared GEMM's at 64.
+      // Elsewhere it only ties the schedule (bf16 decode of few chunks, shared GEMM
+      // past 256 rows: 2 % slower)
+      if constexpr ((G == 8 && !kMfma && !kRing) || kShare == 1)
+        asm volatile("" : "+v"(ow[d]));
       if constexpr (kCK > 0 && d == 0) {
         if (kFirst || (kTail && r == 0)) first_dw = ow[0];
       }
@@ -1013,10 +1016,11 @@ __device__ __forceinline__ void decode_chunks(const LaunchArgs& a, const DevTens
           }
           if constexpr (kShare) {
             // this wave's operands to the multiplying waves, once they have left this
-            // half of the buffer
+            // buffer
             const uint32_t pair = r >> 1;
-            if (pair >= 2) share_wait(sh->pairs_multiplied, kShareMultiply, pair - 1);
-            u32x4* frag = sh->frag + (pair & 1u) * (kShareTiles * 2 * 64);
+            if (pair >= kShare)
+              share_wait(sh->pairs_multiplied, kShareMultiply, pair + 1 - kShare);
+            u32x4* frag = sh->frag + (pair & (kShare - 1u)) * (kShareTiles * 2 * 64);
             frag[(2 * sh->wave) * 64 + lane] = u32x4{b0[0], b0[1], b0[2], b0[3]};
             frag[(2 * sh->wave + 1) * 64 + lane] = u32x4{b1[0], b1[1], b1[2], b1[3]};
             set_counter(sh->pairs_written + 4u * sh->wave, pair + 1);

@@ -126,22 +126,39 @@ __global__ __launch_bounds__(kThreads) void wc_gemv_w4n_kernel(LaunchArgs a) {
 // x rows 32 kXB w .. of the pass.  Every tile must be full: 64 rows, tile_c
 // columns.  DevTensor::x is the packed x of the job (pack_x_kernel).
 //
-// 128 registers a wave leave one such workgroup to a compute unit, so what bounds
-// it is the chain of its eight decoding waves, whose steps are those of wc_ring.h
-// with the words prepared by the wave itself.  Multiplying in waves of their own
-// hides the products behind the decode and halves the passes above 256 rows, where
-// eight waves that did both held 256 rows at most: 8B bf16 layer, m = 80 / 256 /
-// 512 / 1000: 0.266 / 0.307 / 0.499 / 0.943 ms before, 0.254 / 0.298 / 0.407 /
-// 0.668 now.
+// What bounds it is the chain of its eight decoding waves, whose steps are those of
+// wc_ring.h with the words prepared by the wave itself, and with two of them to a
+// compute unit the LDS.  Multiplying in waves of their own hides the products behind
+// the decode and halves the passes above 256 rows, where eight waves that did both
+// held 256 rows at most: 8B bf16 layer, m = 80 / 256 / 512 / 1000: 0.255 / 0.303 /
+// 0.492 / 0.917 ms with those, 0.188 / 0.246 / 0.375 / 0.659 now.
+//
+// Two layouts.  ShareAlone has a compute unit's LDS to itself.  SharePair halves what a
+// workgroup takes (64 registers, half the ring, one operand buffer) so that two run
+// there, which only pays when there are more workgroups than compute units: up to
+// that many, SharePair / ShareAlone take 72 / 64 us (4096 x 4096, m = 256), 90 / 81 us
+// (16 384 x 4096, 256 workgroups); with 264 of them 118 / 136 us, with 448 of one tile
+// 77 / 110 us, of eight 127 / 144 us, with 900 of eight 64-column tiles 82 / 110 us.
+struct ShareAlone {
+  using Ring = OwnRing<2, 4>;
+  static constexpr int kBuffers = 2, kAhead = 4, kWavesPerSimd = 4;
+};
+struct SharePair {
+  using Ring = OwnRing<1, 3>;
+  static constexpr int kBuffers = 1, kAhead = 4, kWavesPerSimd = 8;
+};
 constexpr int kShareThreads = (kShareTiles + kShareMultiply) * 64;
 
-template <int kXB>
-__global__ __launch_bounds__(kShareThreads) void wc_gemm_kernel(LaunchArgs a) {
+template <int kXB, class Layout>
+__global__ __launch_bounds__(kShareThreads)
+__attribute__((amdgpu_waves_per_eu(Layout::kWavesPerSimd))) void wc_gemm_kernel(LaunchArgs a) {
+  using Ring = typename Layout::Ring;
+  constexpr int kBuffers = Layout::kBuffers;
   // the table at LDS address 0, the rings (the prefix sums the table is built from
   // lie in the first, which is filled after the build), the shared operands
-  constexpr uint32_t kRings = 8u * wc::kTableSize, kFrag = kRings + kShareTiles * kOwnRingBytes;
-  static_assert(260 * 4 <= kOwnStaging, "the prefix sums fit the first ring");
-  constexpr uint32_t kCounts = kFrag + 2 * kShareTiles * 2 * 64 * 16;
+  constexpr uint32_t kRings = 8u * wc::kTableSize, kFrag = kRings + kShareTiles * Ring::kBytes;
+  static_assert(260 * 4 <= Ring::kStaging, "the prefix sums fit the first ring");
+  constexpr uint32_t kCounts = kFrag + kBuffers * kShareTiles * 2 * 64 * 16;
   __shared__ __align__(16) uint8_t smem[kCounts + 4 * (kShareTiles + kShareMultiply)];
   uint2* tab = reinterpret_cast<uint2*>(smem);
   const uint32_t wg = blockIdx.x;
@@ -167,7 +184,7 @@ __global__ __launch_bounds__(kShareThreads) void wc_gemm_kernel(LaunchArgs a) {
   if (!multiplies)
     set_counter(s.pairs_written + 4u * wave, wave < s.n_act ? 0u : kShareAll);
   const uint32_t K = T.ntc << T.log_tc;
-  s.first = (pass * kShareTiles + wave) * 32u * kXB;
+  s.first = (pass * kShareMultiply + wave) * 32u * kXB;
   s.mrows = s.first < a.m ? a.m - s.first : 0u;
   // packed x: 1 KiB per (block of 32 rows, pair of columns 16 p ..)
   s.xoff = s.mrows ? ((s.first / 32u) * (K / 16u) * 64u + lane) * 16u +
@@ -184,13 +201,13 @@ __global__ __launch_bounds__(kShareThreads) void wc_gemm_kernel(LaunchArgs a) {
   };
   if (multiplies) {
     build();
-    share_multiply<kXB>(a, T, s, lane);
+    share_multiply<kXB, kBuffers, Layout::kAhead>(a, T, s, lane);
   } else if (wave < s.n_act) {
     const uint32_t chunk = band * T.ntc + seg * kShareTiles + wave;
     const IndexPre pre = load_index(a, T, chunk, 1u);
-    uint32_t* ring = reinterpret_cast<uint32_t*>(smem + kRings + wave * kOwnRingBytes);
-    decode_chunks<2, 64, true, 0, 1, 64, true, 0, OwnRing>(a, T, chunk, lane, tab, ring, pre,
-                                                           build, &s);
+    uint32_t* ring = reinterpret_cast<uint32_t*>(smem + kRings + wave * Ring::kBytes);
+    decode_chunks<2, 64, true, 0, 1, 64, kBuffers, 0, Ring>(a, T, chunk, lane, tab, ring, pre,
+                                                            build, &s);
   } else {
     build();
   }
@@ -286,6 +303,19 @@ bool gemv_wide(int kind, uint64_t tiles) {
   return c.general && c.wide > c.general && tiles > c.general && tiles <= c.wide;
 }
 
+// Compute units of the current device (0 when unknown).
+uint32_t compute_units() {
+  static wc::PerDevice<uint32_t> known;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  return known.get(dev, [&]() -> uint32_t {
+    int cus = 0;
+    return hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess
+               ? uint32_t(cus)
+               : 0u;
+  });
+}
+
 // Rows of x up to which the byte-coded MXFP4 and int4 launches take the 16-wave
 // kernel (in its window): on the 8B layers it gains 3-9 % up to 8 rows, nothing
 // at 12 and loses at 16 rows, where each wave row's conversions and products
@@ -361,10 +391,13 @@ wc_status launch_jobs(const wc::BlobPriv& P, const void* dev_blob, uint32_t n,
         default: hipLaunchKernelGGL((wc_gemv_e5m2_kernel<4>), grid, block, 0, st, args); break;
       }
     } else if (share) {
-      if (pass_rows(m) == 256u)
-        hipLaunchKernelGGL((wc_gemm_kernel<1>), grid, dim3(kShareThreads), 0, st, args);
+      const dim3 threads(kShareThreads);
+      if (pass_rows(m) != 256u)
+        hipLaunchKernelGGL((wc_gemm_kernel<2, ShareAlone>), grid, threads, 0, st, args);
+      else if (wgs <= compute_units())
+        hipLaunchKernelGGL((wc_gemm_kernel<1, ShareAlone>), grid, threads, 0, st, args);
       else
-        hipLaunchKernelGGL((wc_gemm_kernel<2>), grid, dim3(kShareThreads), 0, st, args);
+        hipLaunchKernelGGL((wc_gemm_kernel<1, SharePair>), grid, threads, 0, st, args);
     } else if (rows == 64 && m > kDotRows) {
       if (m <= 32) hipLaunchKernelGGL((wc_gemv_kernel<0, 1, 64>), grid, block, 0, st, args);
       else hipLaunchKernelGGL((wc_gemv_kernel<0, 2, 64>), grid, block, 0, st, args);

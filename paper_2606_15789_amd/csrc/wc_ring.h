@@ -237,21 +237,24 @@ __device__ __forceinline__ void feed(__amdgpu_buffer_rsrc_t rs, uint32_t words, 
 }
 
 // A ring that its decoding wave fills itself, for workgroups with no waves to spare
-// for feeders.  A unit is two blocks of 128 words (one load of a dword a lane each);
-// the ring is two units long and its first unit is written a second time past its
-// end, so p runs on without a wrap while a unit is read and goes back when the
+// for feeders.  A unit is kBlocks blocks of 128 words (one load of a dword a lane
+// each); the ring is two units long and its first unit is written a second time past
+// its end, so p runs on without a wrap while a unit is read and goes back when the
 // second unit is replaced.  Units pass four stages so that no commit waits for what
 // it uses: memory -> LDS staging (loads straight to LDS, kStage units), staging ->
 // registers, registers -> table entries, entries -> ring; each commit moves the
-// units behind it one stage on.
-constexpr uint32_t kOwnBlocks = 2, kOwnStage = 4;
+// units behind it one stage on.  Two blocks to a unit commit half as often, one leaves
+// LDS for a second workgroup (the shared GEMM has both).
 constexpr uint32_t kBlockWordBytes = 256, kBlockRing = 1024;
-constexpr uint32_t kOwnUnitRing = kBlockRing * kOwnBlocks;
-constexpr uint32_t kOwnUnitWords = kBlockWordBytes * kOwnBlocks;  // bytes
-constexpr uint32_t kOwnStaging = 3 * kOwnUnitRing;                // offset of the staging
-constexpr uint32_t kOwnRingBytes = kOwnStaging + kOwnStage * kOwnUnitWords;
 
+template <uint32_t kBlocks, uint32_t kStage>
 struct OwnRing : Entry {
+  static constexpr uint32_t kUnitRing = kBlockRing * kBlocks;
+  static constexpr uint32_t kUnitWords = kBlockWordBytes * kBlocks;  // bytes
+  static constexpr uint32_t kStaging = 3 * kUnitRing;                // offset of the staging
+  static constexpr uint32_t kSlots = kStage * kUnitWords;
+  static constexpr uint32_t kBytes = kStaging + kSlots;
+
   ru4 record;       // buffer descriptor of the chunk's record
   uint32_t ring;    // LDS address
   uint32_t ring_v;  // this lane's place in a block of the ring's first unit
@@ -261,20 +264,26 @@ struct OwnRing : Entry {
   uint32_t thr;     // commit a unit when p passes this
   uint32_t wraps;   // times p went back to the ring's start
   uint32_t slot;    // staging offset of the unit after the next one to commit
-  ru2 g[2 * kOwnBlocks];                    // the next unit's table entries
-  uint32_t w[kOwnBlocks], wn[kOwnBlocks];   // this lane's words (two a block) of the next
+  ru2 g[2 * kBlocks];                    // the next unit's table entries
+  uint32_t w[kBlocks], wn[kBlocks];   // this lane's words (two a block) of the next
                                             // unit and of the one after
-  uint32_t first[4 * kOwnBlocks];           // the chunk's first four units
+  uint32_t first[4 * kBlocks];           // the chunk's first four units
+
+  // A staging offset below 2 kSlots, around the staging's end.
+  __device__ static __forceinline__ uint32_t around(uint32_t x) {
+    if constexpr ((kSlots & (kSlots - 1)) == 0) return x & (kSlots - 1);
+    return x >= kSlots ? x - kSlots : x;
+  }
 
   // The next unit's words to staging offset `to`; past the record they are zeros.
   // The loads have no destination register; the wave waits on vmcnt before it
   // reads the words (commit), and before it ends (close).
   __device__ __forceinline__ void stage(uint32_t to) {
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++) {
+    for (uint32_t b = 0; b < kBlocks; b++) {
       asm volatile("s_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
                    :
-                   : "{m0}"(ring + kOwnStaging + to + b * kBlockWordBytes), "v"(next_v),
+                   : "{m0}"(ring + kStaging + to + b * kBlockWordBytes), "v"(next_v),
                      "s"(record)
                    : "memory");
       next_v += kBlockWordBytes;
@@ -282,7 +291,7 @@ struct OwnRing : Entry {
   }
 
   // Before the workgroup's barrier: the chunk's first words on their way, four
-  // units to registers and the next kOwnStage - 1 to staging.
+  // units to registers and the next kStage - 1 to staging.
   __device__ __forceinline__ void open(uint32_t lds, __amdgpu_buffer_rsrc_t rs, ru4 rec,
                                        uint32_t words_at, uint32_t lane) {
     ring = lds;
@@ -291,76 +300,74 @@ struct OwnRing : Entry {
     lane4 = 4u * lane;
     next_v = words_at + lane4;
 #pragma unroll
-    for (uint32_t k = 0; k < 4 * kOwnBlocks; k++)
+    for (uint32_t k = 0; k < 4 * kBlocks; k++)
       first[k] = __builtin_amdgcn_raw_buffer_load_b32(rs, next_v + k * kBlockWordBytes, 0, 0);
-    next_v += 4 * kOwnUnitWords;
-    constexpr uint32_t kSlots = kOwnStage * kOwnUnitWords;
+    next_v += 4 * kUnitWords;
 #pragma unroll
-    for (uint32_t u = 4; u < 3 + kOwnStage; u++) stage((u * kOwnUnitWords) & (kSlots - 1));
-    slot = 4 * kOwnUnitWords & (kSlots - 1);
+    for (uint32_t u = 4; u < 3 + kStage; u++) stage((u * kUnitWords) % kSlots);
+    slot = 4 * kUnitWords % kSlots;
   }
 
   __device__ __forceinline__ void lookups() {
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++) word_lookups(w[b], g[2 * b], g[2 * b + 1]);
+    for (uint32_t b = 0; b < kBlocks; b++) word_lookups(w[b], g[2 * b], g[2 * b + 1]);
   }
 
   // Units 0 and 1 into the ring, the next ones into their stages, and the lane's
   // first entry, from its state x.
   __device__ __forceinline__ void start(uint32_t x) {
     p = ring;
-    thr = ring + kOwnUnitRing;
+    thr = ring + kUnitRing;
     wraps = 0;
 #pragma unroll
     for (uint32_t u = 0; u < 3; u++) {
 #pragma unroll
-      for (uint32_t b = 0; b < kOwnBlocks; b++) w[b] = first[u * kOwnBlocks + b];
+      for (uint32_t b = 0; b < kBlocks; b++) w[b] = first[u * kBlocks + b];
       lookups();
       if (u == 2) break;
 #pragma unroll
-      for (uint32_t b = 0; b < kOwnBlocks; b++)
-        lds_store4(ring_v + u * kOwnUnitRing + b * kBlockRing,
+      for (uint32_t b = 0; b < kBlocks; b++)
+        lds_store4(ring_v + u * kUnitRing + b * kBlockRing,
                    word_entries(w[b], g[2 * b], g[2 * b + 1]));
     }
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++) wn[b] = first[3 * kOwnBlocks + b];
+    for (uint32_t b = 0; b < kBlocks; b++) wn[b] = first[3 * kBlocks + b];
     begin(x);
   }
 
-  // After every second group j of two steps: they consume at most a unit until the
+  // After every kBlocks groups j of two steps: they consume at most a unit until the
   // next call, and at least a unit is left after it.
   template <int j>
   __device__ __forceinline__ void check() {
-    if constexpr (j % 2 == 1) {
+    if constexpr (j % kBlocks == kBlocks - 1) {
       if (__builtin_expect(p > thr, 0)) commit();
     }
   }
   __device__ __forceinline__ void commit() {
-    const bool head = thr == ring + kOwnUnitRing;  // the ring's first unit is next
+    const bool head = thr == ring + kUnitRing;  // the ring's first unit is next
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++) {
+    for (uint32_t b = 0; b < kBlocks; b++) {
       const ru4 v = word_entries(w[b], g[2 * b], g[2 * b + 1]);
-      lds_store4(ring_v + (head ? 0u : kOwnUnitRing) + b * kBlockRing, v);
-      if (head) lds_store4(ring_v + 2 * kOwnUnitRing + b * kBlockRing, v);
+      lds_store4(ring_v + (head ? 0u : kUnitRing) + b * kBlockRing, v);
+      if (head) lds_store4(ring_v + 2 * kUnitRing + b * kBlockRing, v);
     }
-    p -= head ? 0u : 2 * kOwnUnitRing;
+    p -= head ? 0u : 2 * kUnitRing;
     wraps += head ? 0u : 1u;
-    thr = 2 * ring + 3 * kOwnUnitRing - thr;
+    thr = 2 * ring + 3 * kUnitRing - thr;
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++) w[b] = wn[b];
+    for (uint32_t b = 0; b < kBlocks; b++) w[b] = wn[b];
     lookups();
-    // the unit at `slot` has landed once at most the kOwnStage - 2 units after it
+    // the unit at `slot` has landed once at most the kStage - 2 units after it
     // are in flight; the slot before it is free, its words are in w
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kOwnBlocks * (kOwnStage - 2)) : "memory");
-    constexpr uint32_t kSlots = kOwnStage * kOwnUnitWords;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBlocks * (kStage - 2)) : "memory");
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++)
-      wn[b] = lds_load1(ring + kOwnStaging + slot + b * kBlockWordBytes + lane4);
-    stage((slot - kOwnUnitWords) & (kSlots - 1));
-    slot = (slot + kOwnUnitWords) & (kSlots - 1);
+    for (uint32_t b = 0; b < kBlocks; b++)
+      wn[b] = lds_load1(ring + kStaging + slot + b * kBlockWordBytes + lane4);
+    stage(around(slot + kSlots - kUnitWords));
+    slot = around(slot + kUnitWords);
     // keep the words in their registers: no copies on the path without a commit
 #pragma unroll
-    for (uint32_t b = 0; b < kOwnBlocks; b++) asm volatile("" : "+v"(w[b]), "+v"(wn[b]));
+    for (uint32_t b = 0; b < kBlocks; b++) asm volatile("" : "+v"(w[b]), "+v"(wn[b]));
   }
 
   template <bool kAll>
@@ -369,7 +376,7 @@ struct OwnRing : Entry {
   }
 
   __device__ __forceinline__ uint32_t words() const {
-    return (wraps * 2 * kOwnUnitRing + (p - ring)) / 8u;
+    return (wraps * 2 * kUnitRing + (p - ring)) / 8u;
   }
 
   // No load may be in flight to the wave's LDS when it ends.

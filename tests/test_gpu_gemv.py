@@ -340,6 +340,44 @@ def test_shared_gemm_around_its_passes(dev, m, words):
         _check(_run_gemm(blob, dev, 0, x), w, x)
 
 
+def _rare_exponents(rng, shape, bands):
+    """bf16 words of which the given bands (64 rows each) hold nothing but 200
+    exponents that are rare in the whole, 12 bits a symbol or nearly: the most stream
+    words a step can take, step after step."""
+    exps = np.full(shape, 120)
+    for b in bands:
+        exps[64 * b: 64 * b + 64] = rng.integers(27, 228, (64, shape[1]))
+    return ((rng.integers(0, 2, shape) << 15) | (exps << 7) |
+            rng.integers(0, 128, shape)).astype(np.uint16)
+
+
+def _most_words(blob, symbols):
+    """The most stream words a step of any chunk of the blob's first tensor takes."""
+    raw = blob.tobytes()
+    info = oracle.tensor_info(raw)[0]
+    idx = struct.unpack_from("<Q", raw, 32)[0]
+    nw = [struct.unpack_from("<I", raw, 16 * struct.unpack_from("<I", raw, idx + 4 * c)[0])[0]
+          for c in range(info["n_chunks"])]
+    return max(nw) * 64 / symbols
+
+
+@pytest.mark.parametrize("m", [65, 128, 256])
+def test_shared_gemm_two_workgroups_to_a_compute_unit(dev, m):
+    """Up to 256 rows of x, launches of more workgroups than compute units take the
+    layout of which two fit one: 8 workgroups more (3 tiles of 16 columns, 10 of 32 in
+    two segments, one of 512), with a first and last band of the most stream words."""
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    rng = np.random.default_rng(77 + m)
+    for bands, cols, tile_c in [(cus + 8, 48, 16), (cus // 2 + 4, 320, 32), (cus + 1, 512, 512)]:
+        shape = (64 * bands, cols)
+        say("shared gemm, two workgroups a compute unit", m, shape, tile_c)
+        w = _rare_exponents(rng, shape, [0, bands - 1])
+        x = _bf16(rng.integers(-3, 4, (m, cols)).astype(np.float32))
+        blob = wc.encode([("bf16", w, shape)], tile=(64, tile_c), tile_order=1)
+        assert _most_words(blob, 64 * tile_c) > 47  # 64 lanes, 12 bits each: 48
+        _check(_run_gemm(blob, dev, 0, x), w, x)
+
+
 def test_shared_gemm_full_size_layer(dev):
     """All seven projections of a Llama-3-70B layer (numpy draw), 64 x 512
     tiles, 256 rows of x, one launch: sampled y within the fp32 bound."""
