@@ -253,6 +253,12 @@ __global__ __launch_bounds__(kHistThreads) void hist_kernel(EncArgs a) {
 // workgroup counts its first kSafeWords words, which cannot overflow, and goes on
 // into the same counters when the largest of them, in proportion, leaves room;
 // otherwise, or when the sum turns out wrong, it counts in pieces of kSafeWords.
+//
+// Adds to one dword are done one after the other, and two words share it: where an
+// eighth of a wave's lanes or more hold the first one's word, lanes with the same word
+// add up first (the first two such words of a wave, one add each).  117 MB of words 0
+// and 1 took 321 us a call without, of one word 318 (four passes in dwords 286 and
+// 380), 190 and 146 now; 117 MB of weights 122 and 124.
 constexpr int kWordThreads = 1024;
 constexpr int kWordLoads = 2;              // 16-byte loads in flight per lane
 constexpr uint64_t kSafeWords = 65528;     // below 2^16, whole 16-byte loads
@@ -278,6 +284,30 @@ __global__ __launch_bounds__(kWordThreads) void word_hist_kernel(uint64_t src, u
     if (n > 0) atomicAdd(&c[(two & 0xFFFFu) >> 1], two & 1u ? 0x10000u : 1u);
     if (n > 1) atomicAdd(&c[two >> 17], two & 0x10000u ? 0x10000u : 1u);
   };
+  // the same where few words make up most: lanes with the same word add once
+  auto add_alike = [&](uint32_t two) {
+#pragma unroll
+    for (uint32_t h = 0; h < 2; h++) {
+      const uint32_t w = h ? two >> 16 : two & 0xFFFFu;
+      bool left = true;
+#pragma unroll
+      for (int r = 0; r < 2; r++) {
+        const uint64_t m = __ballot(left);
+        if (!m) break;
+        const int lead = __ffsll((unsigned long long)m) - 1;
+        const uint32_t v = __builtin_amdgcn_readlane(w, lead);
+        const bool same = left && w == v;
+        const uint32_t k = __popcll(__ballot(same));
+        if (int(__lane_id()) == lead) atomicAdd(&c[v >> 1], v & 1u ? k << 16 : k);
+        left = left && !same;
+      }
+      if (left) atomicAdd(&c[w >> 1], w & 1u ? 0x10000u : 1u);
+    }
+  };
+  auto alike = [&](uint32_t two) {  // of the wave's lanes, an eighth or more
+    const uint32_t w = two & 0xFFFFu;
+    return __popcll(__ballot(w == uint32_t(__builtin_amdgcn_readfirstlane(w)))) >= 8;
+  };
   auto count = [&](uint64_t o0, uint64_t o1) {  // o0: a multiple of 16
     constexpr uint64_t kStep = kWordThreads * 16ull;
     const uint64_t full = o0 + (o1 - o0) / 16 * 16;
@@ -287,9 +317,17 @@ __global__ __launch_bounds__(kWordThreads) void word_hist_kernel(uint64_t src, u
 #pragma unroll
       for (int u = 0; u < kWordLoads; u++) v[u] = *(gu4*)(uint64_t)(p + off + u * kStep);
 #pragma unroll
-      for (int u = 0; u < kWordLoads; u++)
+      for (int u = 0; u < kWordLoads; u++) {
+        if (alike(v[u][0])) {
+          // a loop: unrolled, its code took registers and 5 % from the other branch
+#pragma unroll 1
+          for (int d = 0; d < 4; d++)
+            add_alike(d < 2 ? (d ? v[u][1] : v[u][0]) : (d == 2 ? v[u][2] : v[u][3]));
+        } else {
 #pragma unroll
-        for (int d = 0; d < 4; d++) add(v[u][d], 2u);
+          for (int d = 0; d < 4; d++) add(v[u][d], 2u);
+        }
+      }
     }
     for (; off < o1; off += kStep) {
       const uint4 v = load16(p, o1, off);

@@ -226,8 +226,8 @@ constexpr uint32_t kMaxGemmRows = 4096;
 // Rows of x of a pass of the shared fused GEMM: up to 256 every multiplying wave
 // has one block of 32, above two.  With two, fewer passes decode the weights again,
 // but fewer waves multiply where 256 rows are enough.  8B bf16 layer, one block / two:
-// 0.254 / 0.266 ms at m = 80, 0.299 / 0.299 at 256, 0.483 / 0.407 at 512, 0.913 /
-// 0.668 at 1000.
+// 0.184 / 0.245 ms at m = 80, 0.243 / 0.270 at 256, 0.403 / 0.372 at 512, 0.752 /
+// 0.638 at 1000 (70B: 0.756 / 0.860 at 256, 1.467 / 1.323 at 512).
 constexpr uint32_t pass_rows(uint32_t m) { return m <= 256 ? 256u : 512u; }
 
 namespace {

@@ -464,3 +464,19 @@ def test_tensors_around_a_launchs_limit(dev, n, gaps):
         entries.append((["bf16", "u8", "u4", "fp8_e4m3"][i % 4],
                         rng.normal(128, 9, size).astype(np.uint8)))
     assert_same_blob(entries, dev, chunk_bytes=4096)
+
+
+@pytest.mark.parametrize("n", [1, 65, 8 * 1024 * 2 + 3, 1_000_001, 20_000_003])
+@pytest.mark.parametrize("words", [(7,), (0, 1), (0x3F80, 0xBF80, 0), (1, 2, 3, 4, 5, 0xFFFF)])
+def test_analyze_device_of_few_words(dev, n, words):
+    """16-bit tensors of few different words, whose counts the lanes of a wave add up
+    before they add them to a counter: neighbours that share a dword of counters, an
+    uneven mix, sizes with a last load of 1 to 8 words, and (the largest) several pieces
+    of a counter's range to a workgroup."""
+    say("few words", n, words)
+    rng = np.random.default_rng(n + len(words))
+    p = np.arange(1, len(words) + 1, dtype=np.float64)
+    d = rng.choice(np.array(words, np.uint16), n, p=p / p.sum())
+    if n > 1000:  # a stretch of everything
+        d[n // 2: n // 2 + 500] = rng.integers(0, 65536, 500)
+    _same_stats(wc.analyze_device("bf16", to_dev(d, dev)), wc.analyze("bf16", d))
