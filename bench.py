@@ -308,7 +308,8 @@ def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool, out_bytes=
     exceed the general kernel's resident waves (24 a compute unit: the LDS of
     three 8-wave workgroups) but fit the 16-wave kernel's (32 a compute unit),
     its kernel for few chunks (64 lanes; up to four a compute unit, or at most
-    one workgroup of eight; 32 steps of 64 symbols in the longest), the general
+    one workgroup of eight and, of bytes or of 16-bit words in fewer than 256
+    steps, 5.5 chunks; 32 steps of 64 symbols in the longest), the general
     kernel otherwise.  `out_bytes`: the decoded bytes of each tensor (None: the
     chunks are one tensor's and full).  The library takes the same decision
     from the runtime's occupancy figures."""
@@ -318,7 +319,12 @@ def decode_kernel_for(dtypes, n_chunks: int, lanes: int, tiled: bool, out_bytes=
     per_byte = {"bf16": 0.5, "fp16": 0.5, "u4": 2, "fp4_e2m1": 2}
     steps = max(min(b, chunk_bytes) * per_byte.get(d, 1) / 64 for d, b in sizes)
     workgroups = sum(-(-b // (8 * chunk_bytes)) for _, b in sizes)
-    if lanes == 64 and steps > 31 and (n_chunks <= 4 * cus or workgroups <= cus):
+    short16 = chunk_bytes < 256 * 64 * 2
+    work = sum(-(-b // chunk_bytes) * (16 if per_byte.get(d, 1) == 1
+                                       or (per_byte[d] == 0.5 and short16) else 11)
+               for d, b in sizes)
+    if lanes == 64 and steps > 31 and (n_chunks <= 4 * cus or
+                                       (workgroups <= cus and work <= 88 * cus)):
         return "wc_decode_small_kernel"
     if (all(d in ("bf16", "fp16") for d in dtypes) and lanes == 64 and not tiled
             and 24 * cus < n_chunks <= 32 * cus):

@@ -116,7 +116,18 @@ struct BlobPriv {
 // Chunks of fewer than kSmallSteps steps are over before the feeders have paid for
 // their start: 1024 bf16 chunks of 8 steps take 8.4 us there and 7.9 on the general
 // kernel, int8 chunks of 16 steps 8.9 and 8.5, of 32 steps 9.8 and 10.0.
-constexpr uint32_t kSmallChunks = 8, kFewChunks = 4, kSmallSteps = 32;
+//
+// Two decodes at once, on two streams, bound the small kernel by its LDS accesses, of
+// which a step has more than one of the general kernel (the feeders' lookups, one for
+// every word): two launches of 1792 chunks together / one alone, general and small,
+// 64 KiB int8 chunks 117 and 150 / 97 and 83 us, bf16 80 and 88 / 62 and 48, int4 215
+// and 224 / 181 and 123; of 1340, 116 and 119 / 97 and 82, 75 and 71 / 61 and 47,
+// 214 and 176 / 180 and 122.  It is kept while a launch alone gains more than two
+// lose: int8, with the most words to a step, up to 5.5 chunks to a compute unit, and
+// so 16-bit chunks of fewer than kLongSteps steps (1700 of 16 KiB: 36 and 43 / 27 and
+// 23 us), the others up to 8.
+constexpr uint32_t kSmallChunks = 8, kFewChunks = 4, kSmallSteps = 32, kLongSteps = 256;
+constexpr uint32_t kHeavy = 16, kLight = 11, kSmallWork = 88;  // 88 = 5.5 x 16 = 8 x 11
 
 enum class DecodeKernel { kGeneral, kWide, kSmall, kFew };
 
@@ -125,7 +136,7 @@ struct DecodeCapacity {
 };
 
 struct DecodeLaunch {
-  uint64_t chunks = 0, small_wgs = 0;
+  uint64_t chunks = 0, small_wgs = 0, work = 0;
   uint64_t steps = 0;  // of the longest chunk
   bool lanes64 = true, wide_fits = true;
 
@@ -134,6 +145,9 @@ struct DecodeLaunch {
     small_wgs += (T.n_chunks + kSmallChunks - 1) / kSmallChunks;
     const uint64_t symbols = T.n_sym < T.sym_per_chunk() ? T.n_sym : T.sym_per_chunk();
     if (symbols > steps * T.lanes) steps = (symbols + T.lanes - 1) / T.lanes;
+    const bool heavy = is_byte(T.dtype) || (has_raw(T.dtype) &&
+                                            T.sym_per_chunk() < uint64_t(kLongSteps) * T.lanes);
+    work += T.n_chunks * (heavy ? kHeavy : kLight);
     lanes64 = lanes64 && T.lanes == 64;
     wide_fits = wide_fits && has_raw(T.dtype) && T.lanes == 64 && !T.tile_r;
   }
@@ -144,7 +158,7 @@ struct DecodeLaunch {
       return DecodeKernel::kWide;
     if (steps < kSmallSteps) return DecodeKernel::kGeneral;
     if (chunks <= cap.cus * kFewChunks) return DecodeKernel::kFew;
-    if (small_wgs <= cap.cus) return DecodeKernel::kSmall;
+    if (small_wgs <= cap.cus && work <= cap.cus * kSmallWork) return DecodeKernel::kSmall;
     return DecodeKernel::kGeneral;
   }
 };

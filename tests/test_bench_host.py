@@ -55,6 +55,8 @@ def test_decode_kernel_for_few_chunks(bench, cus_256):
     assert name([1]) == name([2048]) == name([64] * 32) == "wc_decode_small_kernel"
     assert name([2049]) == name([65] * 30) == "wc_decode_kernel"
     assert name([1], 1024) == "wc_decode_small_kernel" and name([1], 512) == "wc_decode_kernel"
+    u8 = lambda n: bench.decode_kernel_for(["u8"], n, 64, False)  # noqa: E731
+    assert u8(1408) == "wc_decode_small_kernel" and u8(1409) == "wc_decode_kernel"
     assert bench.decode_kernel_for(["u4"], 1, 32, False) == "wc_decode_kernel"
     assert bench.decode_kernel_for(["u4"], 1, 64, True) == "wc_decode_small_kernel"
 

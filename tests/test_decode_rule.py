@@ -90,7 +90,7 @@ def test_small_workgroups_beyond_the_compute_units_are_no_second_round(rule):
 def test_short_chunks_take_the_general_kernel(rule):
     """A launch whose longest chunk has fewer than 32 steps (2048 symbols)."""
     for dtype, nbytes in [("bf16", 4096), ("u8", 2048), ("u4", 1024)]:
-        for n, chunks in [("few", 1000), ("small", 2000)]:
+        for n, chunks in [("few", 1000), ("small", 1300)]:
             assert rule([(dtype, chunks)], chunk_bytes=nbytes) == n
             assert rule([(dtype, chunks)], chunk_bytes=nbytes // 2) == "general"
     # one chunk that its tensor does not fill
@@ -145,3 +145,15 @@ def test_device_figures_are_kept_without_an_allocation(tmp_path):
                     "-I" + os.path.join(ROOT, "paper_2606_15789_amd", "csrc"), str(src),
                     "-o", str(exe)], check=True, capture_output=True, text=True)
     assert subprocess.run([str(exe)]).returncode == 0
+
+
+def test_overlapping_launches_of_many_words_a_step_take_the_general_kernel(rule):
+    """From 5.5 chunks to a compute unit (int8, fp8 and short 16-bit chunks)."""
+    assert rule([("u8", 1408)]) == rule([("fp8_e4m3", 1408)]) == "small"
+    assert rule([("u8", 1409)]) == rule([("fp8_e4m3", 1409)]) == "general"
+    assert rule([("bf16", 1408)], chunk_bytes=16384) == "small"
+    assert rule([("bf16", 1409)], chunk_bytes=16384) == "general"
+    assert rule([("bf16", 2048)], chunk_bytes=32768) == "small"
+    assert rule([("u4", 2048)], chunk_bytes=4096) == "small"
+    assert rule([("u4", 1400), ("u8", 400)]) == "small"    # 11 x 1400 + 16 x 400 <= 88 x 256
+    assert rule([("u4", 1400), ("u8", 456)]) == "general"
