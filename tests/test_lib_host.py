@@ -426,8 +426,8 @@ def test_device_encoder_rejects_before_any_launch():
 
 @pytest.mark.parametrize("fmt", sorted(wc.DTYPES))
 def test_blob_shapes_and_formats_from_the_descriptors(fmt):
-    """shape and dtype of every tensor of a blob, and none past its bytes or before
-    them."""
+    """shape and dtype of every tensor of a blob, and of no other: the bytes next to
+    the descriptors are the header and the tables."""
     nbytes = 2 * 64 * 64
     per = {"bf16": 2, "fp16": 2}.get(fmt)
     cols = 64 if per else (256 if fmt in ("u4", "fp4_e2m1") else 128)
@@ -435,11 +435,13 @@ def test_blob_shapes_and_formats_from_the_descriptors(fmt):
     blob = wc.encode([(fmt, w, (64, cols)), (fmt, w[:0]), (fmt, w)])
     assert [blob.shape(np.int64(t)) for t in range(3)] == [(64, cols), (0, 0), (0, 0)]
     assert [blob.dtype(t) for t in range(3)] == [fmt] * 3
-    for t in (-1, 1 << 20):
+    for t in (-1, -2, -3, 3, 4, 1 << 20):
         with pytest.raises(IndexError):
             blob.shape(t)
         with pytest.raises(IndexError):
             blob.dtype(t)
+    with pytest.raises(TypeError):
+        blob.shape(0.5)
     blob.free()
     with pytest.raises(ValueError):
         blob.shape(0)
