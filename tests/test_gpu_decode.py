@@ -221,10 +221,14 @@ def test_launches_around_the_wide_kernels_window(dev, rows, cols, dtype):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("lanes", [64, 32])
-def test_device_side_corruption_flags(dev, lanes):
-    """The kernel's own checks turn corrupted device bytes into error bits."""
+@pytest.mark.parametrize("lanes,more", [(64, False), (32, False), (64, True)])
+def test_device_side_corruption_flags(dev, lanes, more):
+    """The kernel's own checks turn corrupted device bytes into error bits: on the
+    kernel for few chunks, that for 32 lanes and (with more chunks in the launch) the
+    general one."""
     pairs = [(t.dtype, t.data) for t in synth.config(1, div=8)]
+    if more:  # after the tensor that is corrupted
+        pairs += _with_more_chunks(dev, [], 16384)
     blob = wc.encode(pairs, chunk_bytes=16384, lanes=lanes)
     raw = blob.tobytes()
     idx = struct.unpack_from("<Q", raw, 32)[0]
@@ -330,8 +334,9 @@ def _rare_symbols(dtype, chunks):
 @pytest.mark.parametrize("chunks", [1, 1024, 1025, 2048, 2049])
 def test_launches_around_the_small_kernels_limits(dev, chunks, dtype, tile):
     """Up to four, up to eight and more 64-lane chunks to a compute unit (256 on
-    an MI355X) run on different kernels: whole and ragged chunks of 1 KiB, byte
-    runs and both tile orders, every symbol width, words at the highest rate."""
+    an MI355X): whole and ragged chunks of 1 KiB, byte runs and both tile orders,
+    every symbol width.  4-bit chunks have 32 steps and run on a kernel for each of
+    the three; bf16 and 8-bit ones (8 and 16 steps) all on the general kernel."""
     say("small kernel", chunks, dtype, tile)
     d = _rare_symbols(dtype, chunks)
     if tile is None:
@@ -344,3 +349,129 @@ def test_launches_around_the_small_kernels_limits(dev, chunks, dtype, tile):
     blob = wc.encode(entries, chunk_bytes=1024, **kw)
     assert blob.n_chunks == chunks
     check_exact([(dtype, d)], blob, gpu_decode(blob, dev))
+
+
+def _cus(dev):
+    return torch.cuda.get_device_properties(dev).multi_processor_count
+
+
+def _launch_kernel(chunks, dtype, cb, cus):
+    """The kernel of an untiled or tiled launch of 64-lane chunks of at least 32 steps,
+    as test_decode_rule.py has it for wc_decode's rule."""
+    heavy = dtype == "u8" or (dtype == "bf16" and cb < 32768)
+    if chunks <= 4 * cus:
+        return "few"
+    return "small" if chunks <= 8 * cus and 2 * chunks <= (11 if heavy else 16) * cus else "general"
+
+
+@pytest.mark.parametrize("tile", [None, 0, 1])
+@pytest.mark.parametrize("dtype", ["bf16", "u8", "u4"])
+@pytest.mark.parametrize("kernel,per_cu", [("few", 1.25), ("small", 5.25), ("general", 8.25)])
+def test_words_at_the_highest_rate(dev, kernel, per_cu, dtype, tile):
+    """A chunk of symbols that have one slot of the table's 4096, 12 bits each: 48 of
+    64 lanes take a word in the mean step, or 64 of 64 in three steps of four where all
+    lanes decode the same ones.  Of 16 KiB, so that a ring of 1024 entries is filled six
+    to 24 times over: its wraps, the entries that stand twice and a feeder that has to
+    wait, on each of the kernels for 64-lane chunks, byte runs and both tile orders."""
+    cus = _cus(dev)
+    chunks, cb = int(per_cu * cus), 16384
+    assert _launch_kernel(chunks, dtype, cb, cus) == kernel
+    cols = {"bf16": 128, "u8": 256, "u4": 512}[dtype]  # 64 x cols symbols: 16 KiB
+    for alike in (False, True):
+        say("highest rate", kernel, chunks, dtype, tile, alike)
+        rng = np.random.default_rng(chunks + alike)
+        if dtype == "bf16":  # exponents 1..255, any sign and mantissa
+            e = rng.integers(1, 256, cb // 2)
+            rare = (rng.integers(0, 2, e.size) << 15 | e << 7 |
+                    rng.integers(0, 128, e.size)).astype(np.uint16).view(np.uint8)
+        elif dtype == "u8":
+            rare = rng.integers(1, 256, cb, dtype=np.uint8)
+        else:
+            rare = rng.integers(1, 16, (2, cb), dtype=np.uint8)
+            rare = rare[0] * 16 + rare[1]
+        if alike:  # a lane takes 16 bytes of each KiB, of a row in column blocks
+            rare = (np.tile(rare[:cb // 64], 64) if tile == 1 else
+                    np.repeat(rare.reshape(16, 64, 16)[:, :1], 64, axis=1).reshape(-1))
+        d = np.zeros((chunks, cb), np.uint8)
+        d[chunks // 3] = rare
+        d = d.reshape(-1)
+        if tile is None:
+            entries, kw = [(dtype, d)], {}
+        else:
+            entries, kw = [(dtype, d, (64 * chunks, cols))], {"tile": (64, cols),
+                                                              "tile_order": tile}
+        blob = wc.encode(entries, chunk_bytes=cb, **kw)
+        assert blob.n_chunks == chunks
+        raw = blob.tobytes()
+        idx = struct.unpack_from("<Q", raw, 32)[0]
+        words, = struct.unpack_from("<I", raw, 16 * struct.unpack_from(
+            "<I", raw, idx + 4 * (chunks // 3))[0])
+        assert words > 5 * 1024 and words / cols > 46, words  # of 48, less the first states
+        out, = gpu_decode(blob, dev)
+        assert np.array_equal(out.cpu().numpy(), d)
+
+
+# The cases above that have up to eight chunks to a compute unit run on the kernels
+# for few chunks.  A tensor of more in the same launch takes them to the general one.
+
+def _with_more_chunks(dev, pairs, cb):
+    return [("u8", np.full((8 * _cus(dev) + 1) * cb, 9, np.uint8))] + list(pairs)
+
+
+def _check_after_more_chunks(dev, pairs, blob):
+    assert blob.n_tensors <= 32  # one launch
+    outs = gpu_decode(blob, dev)
+    assert bool((outs[0] == 9).all())
+    raw = blob.tobytes()
+    for t, (p, n) in enumerate(zip(pairs, [i["n_chunks"] for i in oracle.tensor_info(raw)][1:])):
+        got = outs[t + 1].cpu().numpy()
+        assert np.array_equal(got, np.ascontiguousarray(p[1]).view(np.uint8).reshape(-1)), (t, p[0])
+        if n:
+            assert np.array_equal(got, oracle.decode_chunks(raw, t + 1, 0, n)), (t, p[0])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16", "u8", "u4", "fp8_e4m3", "fp4_e2m1"])
+@pytest.mark.parametrize("cb", [256, 16384])
+def test_general_kernel_edge_sizes(dev, dtype, cb):
+    rng = np.random.default_rng(2)
+    esize = 2 if dtype in ("bf16", "fp16") else 1
+    E = cb // esize
+    pairs = []
+    for n in [0, 1, 2, 3, 5, 63, 64, 65, 127, 128, 129, 255, 257, E - 1, E, E + 1, 2 * E + 7, 3 * E]:
+        if esize == 2:
+            d = (rng.normal(0, 0.02, n).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+        else:
+            d = rng.integers(0, 256, n).astype(np.uint8)
+            d[: n // 2] = 3
+        pairs.append((dtype, d))
+    say("general kernel, edge sizes", dtype, cb)
+    blob = wc.encode(_with_more_chunks(dev, pairs, cb), chunk_bytes=cb)
+    _check_after_more_chunks(dev, pairs, blob)
+
+
+def test_general_kernel_bit_patterns_and_degenerate_tables(dev):
+    rng = np.random.default_rng(3)
+    allw = rng.permutation(np.arange(65536, dtype=np.uint32)).astype(np.uint16)
+    allb = rng.permutation(np.repeat(np.arange(256, dtype=np.uint8), 400))
+    pairs = [("bf16", allw), ("fp16", allw[::-1].copy())]
+    pairs += [(dt, allb) for dt in ("u8", "u4", "fp8_e4m3", "fp8_e5m2", "fp4_e2m1")]
+    pairs += [("u8", np.full(200_000, 42, np.uint8)), ("u4", np.full(70_000, 0x77, np.uint8)),
+              ("bf16", np.full(50_000, 0x3F80, np.uint16)),
+              ("u8", np.concatenate([np.zeros(100_000, np.uint8), np.arange(256, dtype=np.uint8)]))]
+    say("general kernel, bit patterns and degenerate tables")
+    blob = wc.encode(_with_more_chunks(dev, pairs, 16384), chunk_bytes=16384)
+    _check_after_more_chunks(dev, pairs, blob)
+
+
+@pytest.mark.parametrize("tile", [(32, 128), (64, 256), (128, 256), (1, 256)])
+@pytest.mark.parametrize("order", [0, 1])
+def test_general_kernel_tiles(dev, tile, order):
+    say("general kernel, tiles", tile, order)
+    pairs = _shaped(synth.config(2, div=8)[:7] + synth.config(3, div=8))
+    rng = np.random.default_rng(5)  # 8-bit tiles: those workloads have none
+    pairs.append(("u8", np.clip(rng.normal(100, 9, (256, 512)), 0, 255).astype(np.uint8), (256, 512)))
+    blob = wc.encode(_with_more_chunks(dev, pairs, 16384), chunk_bytes=16384, tile=tile,
+                     tile_order=order)
+    tiled = {i["dtype"] for i in oracle.tensor_info(blob.tobytes()) if i["tile"] == tile}
+    assert len(tiled) == (3 if tile[0] > 1 else 2), tiled  # 1 x 256 nibbles: too small a chunk
+    _check_after_more_chunks(dev, pairs, blob)

@@ -326,9 +326,8 @@ def test_shared_gemm_small_integers_exact(dev, m):
 @pytest.mark.parametrize("m", [96, 256, 257, 512, 513])
 def test_shared_gemm_around_its_passes(dev, m, words):
     """One block of 32 x rows a multiplying wave up to 256 rows, two above; exponents
-    that cost no stream words (one value) or nearly the most (201 values, all alike
-    often), so the decoding waves commit no words or as many as they can; 3 tiles of
-    16 columns (one pair each), 10 of 32 and 9 of 512."""
+    that cost no stream words (one value) or many (201 values, all alike often: 7.6 of
+    at most 12 bits); 3 tiles of 16 columns (one pair each), 10 of 32 and 9 of 512."""
     rng = np.random.default_rng(900 + m)
     for shape, tile in [((64, 48), (64, 16)), ((128, 320), (64, 32)), ((64, 4608), (64, 512))]:
         say("shared gemm passes", m, words, shape)
@@ -376,6 +375,29 @@ def test_shared_gemm_two_workgroups_to_a_compute_unit(dev, m):
         blob = wc.encode([("bf16", w, shape)], tile=(64, tile_c), tile_order=1)
         assert _most_words(blob, 64 * tile_c) > 47  # 64 lanes, 12 bits each: 48
         _check(_run_gemm(blob, dev, 0, x), w, x)
+
+
+@pytest.mark.parametrize("m", [96, 256, 300, 1000])
+def test_shared_gemm_words_at_the_highest_rate(dev, m):
+    """At most a workgroup to a compute unit, or more than 256 rows of x: the layout that
+    has a compute unit to itself, with a band of the most stream words a step can take
+    and one in which all lanes (W rows) decode the same exponents, so that three steps of
+    four take 64 words."""
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    bands = cus // 2
+    for cols, tile_c in [(1024, 512), (64, 32)]:
+        shape = (64 * bands, cols)
+        say("shared gemm, the most words", m, shape, tile_c)
+        rng = np.random.default_rng(55 + m)
+        w = _rare_exponents(rng, shape, [0, bands - 1])
+        w[64:128] = w[:1] & 0x7F80 | w[64:128] & 0x807F
+        x = _bf16(rng.integers(-3, 4, (m, cols)).astype(np.float32))
+        blob = wc.encode([("bf16", w, shape)], tile=(64, tile_c), tile_order=1)
+        if tile_c == 512:  # (a tile of 32 columns has 32 steps, and its first words in its states)
+            assert _most_words(blob, 64 * tile_c) > 47  # 64 lanes, 12 bits each: 48
+        y = _run_gemm(blob, dev, 0, x)
+        rows = np.r_[0:192, 64 * bands - 64:64 * bands]  # those bands and a plain one
+        _check(y[:, rows], w[rows], x)
 
 
 def test_shared_gemm_full_size_layer(dev):
