@@ -223,8 +223,9 @@ wc_status wc_open(const void* data, uint64_t size, wc_blob** out);
  * a 16-wave-workgroup kernel for that format runs on the latter (the device's
  * occupancy figures are read once per device, with no allocation).  A launch
  * of up to four 64-lane chunks to a compute unit, or of workgroups of eight
- * that all run at once (8-bit formats: up to 5.5 chunks to a compute unit), runs
- * on a kernel for few chunks, in which a second wave per chunk prepares the words.
+ * that all run at once (8-bit formats: up to 5.5 chunks to a compute unit;
+ * column-block tiles of 64 rows and more: up to four), runs on a kernel for few
+ * chunks, in which a second wave per chunk prepares the words.
  * Returns WC_EINVAL (argument mismatch), WC_EUNSUPPORTED (a tensor coded with
  * a lane count other than 64 or 32), WC_EHIP (launch failure). */
 wc_status wc_decode(const wc_blob* desc, const void* dev_blob, void* const* dev_dst, uint32_t n,

@@ -126,8 +126,16 @@ struct BlobPriv {
 // lose: int8, with the most words to a step, up to 5.5 chunks to a compute unit, and
 // so 16-bit chunks of fewer than kLongSteps steps (1700 of 16 KiB: 36 and 43 / 27 and
 // 23 us), the others up to 8.
+//
+// Column-block tiles of 64 rows and more are written 16 bytes a row at a time, which
+// bounds any kernel (0.34 TB/s): up to four chunks to a compute unit the small one is
+// still the faster (64 x 512 bf16, 1024 tiles 200 us against 203), above it is not
+// (1280 tiles 252 and 246, 2048 tiles 395 and 382; 64 x 2048 int4, 1152 tiles 236 and
+// 227).  Tiles of 32 rows keep it (32 x 1024 bf16, 2048 tiles 139 and 181).
 constexpr uint32_t kSmallChunks = 8, kFewChunks = 4, kSmallSteps = 32, kLongSteps = 256;
-constexpr uint32_t kHeavy = 16, kLight = 11, kSmallWork = 88;  // 88 = 5.5 x 16 = 8 x 11
+constexpr uint32_t kTallRows = 64;
+// 88 = 4 x 22 = 5.5 x 16 = 8 x 11
+constexpr uint32_t kTall = 22, kHeavy = 16, kLight = 11, kSmallWork = 88;
 
 enum class DecodeKernel { kGeneral, kWide, kSmall, kFew };
 
@@ -147,7 +155,8 @@ struct DecodeLaunch {
     if (symbols > steps * T.lanes) steps = (symbols + T.lanes - 1) / T.lanes;
     const bool heavy = is_byte(T.dtype) || (has_raw(T.dtype) &&
                                             T.sym_per_chunk() < uint64_t(kLongSteps) * T.lanes);
-    work += T.n_chunks * (heavy ? kHeavy : kLight);
+    const bool tall = T.tile_order == WC_TILE_COLUMN_BLOCKS && T.tile_r >= kTallRows;
+    work += T.n_chunks * (tall ? kTall : heavy ? kHeavy : kLight);
     lanes64 = lanes64 && T.lanes == 64;
     wide_fits = wide_fits && has_raw(T.dtype) && T.lanes == 64 && !T.tile_r;
   }

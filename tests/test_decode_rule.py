@@ -16,7 +16,8 @@ DRIVER = r"""
 #include <stdio.h>
 #include <stdlib.h>
 #include "wc_internal.h"
-// argv: cus, then dtype, decoded bytes, chunk bytes, lanes, tiled of every tensor
+// argv: cus, then dtype, decoded bytes, chunk bytes, lanes, tile rows (0: none; below 0:
+// in column blocks) of every tensor
 int main(int argc, char** argv) {
   const uint64_t cus = strtoull(argv[1], nullptr, 10);
   wc::DecodeLaunch launch;
@@ -26,7 +27,8 @@ int main(int argc, char** argv) {
     T.out_bytes = strtoull(argv[i + 1], nullptr, 10);
     T.chunk_bytes = uint32_t(atoi(argv[i + 2]));
     T.lanes = uint32_t(atoi(argv[i + 3]));
-    T.tile_r = uint32_t(atoi(argv[i + 4]));
+    T.tile_r = uint32_t(abs(atoi(argv[i + 4])));
+    T.tile_order = atoi(argv[i + 4]) < 0 ? WC_TILE_COLUMN_BLOCKS : WC_TILE_ROWS;
     T.n_sym = wc::symbols_of(T.dtype, T.out_bytes);
     T.n_chunks = (T.out_bytes + T.chunk_bytes - 1) / T.chunk_bytes;
     launch.add(T);
@@ -157,3 +159,12 @@ def test_overlapping_launches_of_many_words_a_step_take_the_general_kernel(rule)
     assert rule([("u4", 2048)], chunk_bytes=4096) == "small"
     assert rule([("u4", 1400), ("u8", 400)]) == "small"    # 11 x 1400 + 16 x 400 <= 88 x 256
     assert rule([("u4", 1400), ("u8", 456)]) == "general"
+
+
+def test_tall_column_blocks_take_the_general_kernel_above_four_chunks(rule):
+    for dtype in ("bf16", "u4"):
+        for rows in (-64, -128):
+            assert rule([(dtype, 4 * CUS)], tiled=rows) == "few"
+            assert rule([(dtype, 4 * CUS + 1)], tiled=rows) == "general"
+        for rows in (64, -32, -16):
+            assert rule([(dtype, 8 * CUS)], tiled=rows) == "small"

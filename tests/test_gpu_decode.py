@@ -376,7 +376,8 @@ def test_words_at_the_highest_rate(dev, kernel, per_cu, dtype, tile):
     cus = _cus(dev)
     chunks, cb = int(per_cu * cus), 16384
     assert _launch_kernel(chunks, dtype, cb, cus) == kernel
-    cols = {"bf16": 128, "u8": 256, "u4": 512}[dtype]  # 64 x cols symbols: 16 KiB
+    steps = {"bf16": 128, "u8": 256, "u4": 512}[dtype]  # of 64 symbols: 16 KiB
+    rows, cols = (32, 2 * steps) if tile == 1 else (64, steps)
     for alike in (False, True):
         say("highest rate", kernel, chunks, dtype, tile, alike)
         rng = np.random.default_rng(chunks + alike)
@@ -389,8 +390,9 @@ def test_words_at_the_highest_rate(dev, kernel, per_cu, dtype, tile):
         else:
             rare = rng.integers(1, 16, (2, cb), dtype=np.uint8)
             rare = rare[0] * 16 + rare[1]
-        if alike:  # a lane takes 16 bytes of each KiB, of a row in column blocks
-            rare = (np.tile(rare[:cb // 64], 64) if tile == 1 else
+        if alike:  # a lane takes 16 bytes of each KiB, or of every second 16 of a row
+            rare = (np.tile(np.repeat(rare[:256].reshape(16, 16), 2, axis=0).reshape(-1), 32)
+                    if tile == 1 else
                     np.repeat(rare.reshape(16, 64, 16)[:, :1], 64, axis=1).reshape(-1))
         d = np.zeros((chunks, cb), np.uint8)
         d[chunks // 3] = rare
@@ -398,15 +400,15 @@ def test_words_at_the_highest_rate(dev, kernel, per_cu, dtype, tile):
         if tile is None:
             entries, kw = [(dtype, d)], {}
         else:
-            entries, kw = [(dtype, d, (64 * chunks, cols))], {"tile": (64, cols),
-                                                              "tile_order": tile}
+            entries, kw = [(dtype, d, (rows * chunks, cols))], {"tile": (rows, cols),
+                                                                "tile_order": tile}
         blob = wc.encode(entries, chunk_bytes=cb, **kw)
         assert blob.n_chunks == chunks
         raw = blob.tobytes()
         idx = struct.unpack_from("<Q", raw, 32)[0]
         words, = struct.unpack_from("<I", raw, 16 * struct.unpack_from(
             "<I", raw, idx + 4 * (chunks // 3))[0])
-        assert words > 5 * 1024 and words / cols > 46, words  # of 48, less the first states
+        assert words > 5 * 1024 and words / steps > 46, words  # of 48, less the first states
         out, = gpu_decode(blob, dev)
         assert np.array_equal(out.cpu().numpy(), d)
 
