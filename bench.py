@@ -66,11 +66,11 @@ ROTATE_BYTES = 1 << 30   # resident bytes the small workloads rotate over
 # were taken on (its fingerprint, the hash of its gfx950 assembly that the build
 # writes); otherwise reported as null.
 COUNTED_TRAFFIC = {
-    "llama3-70b-layer-bf16": {"kernel": "wc_decode_kernel", "kernel_fingerprint": "26a86b454521e29a",
-                              "fetch_bytes": 1141265856, "write_bytes": 1738020407},
+    "llama3-70b-layer-bf16": {"kernel": "wc_decode_kernel", "kernel_fingerprint": "957540c7cae0914e",
+                              "fetch_bytes": 1146142930, "write_bytes": 1738021778},
     "llama3-8b-layer-bf16": {"kernel": "wc_decode_wide_kernel",
-                             "kernel_fingerprint": "f89c395c2a6474d3",
-                             "fetch_bytes": 291863961, "write_bytes": 443041996},
+                             "kernel_fingerprint": "372bd04cb0dad58a",
+                             "fetch_bytes": 291936752, "write_bytes": 443042160},
 }
 
 
