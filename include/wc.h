@@ -390,8 +390,8 @@ wc_status wc_gemm_workspace_bytes(const wc_blob* desc, uint32_t n, const uint32_
  * so the fused call pays off up to about 512 rows.  Above that, decode the
  * weights once with wc_decode and multiply with a library GEMM: on one
  * MI355X, for the seven products of a Llama-3-70B layer, the fused call took
- * 0.907 ms at m = 256 against 1.339 ms decode-then-multiply and 1.366 ms at
- * m = 512 against 1.455 ms, but 2.820 ms at m = 1024 against 1.967 ms.  The
+ * 0.826 ms at m = 256 against 1.386 ms decode-then-multiply and 1.394 ms at
+ * m = 512 against 1.486 ms, but 2.737 ms at m = 1024 against 1.982 ms.  The
  * call does not switch by itself.
  * Asynchronous; allocates nothing.  Returns WC_EINVAL (argument, or a
  * workspace too small or misaligned) or WC_EUNSUPPORTED (a tensor the path
