@@ -577,11 +577,12 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 // operands (64 W rows x 16 columns) in LDS, and while the next pair is decoded, every
 // multiplying wave takes all of them times its own kXB blocks of 32 x rows, so that
 // the matrix cores work beside the decode.  With two LDS buffers the next pair goes to
-// the other one; with one it waits in registers until the last is multiplied.  Each wave publishes how many pairs it has written or multiplied,
-// and the waves wait for each other's counts, not for all waves at a barrier: a
-// decoding wave that commits words (wc_ring.h) in one pair may catch up in the next
-// (2 % on the 8B layer at m = 80).  The waits end: the pair a wave waits for never
-// waits for a later one, and a wave that leaves early publishes kShareAll.
+// the other one; with one it waits in registers until the last is multiplied.  Each
+// wave publishes how many pairs it has written or multiplied, and the waves wait for
+// each other's counts, not for all waves at a barrier: a decoding wave that commits
+// words (wc_ring.h) in one pair may catch up in the next (2 % on the 8B layer at m =
+// 80).  The waits end: the pair a wave waits for never waits for a later one, and a
+// wave that leaves early publishes kShareAll.
 constexpr int kShareTiles = 8;
 constexpr int kShareMultiply = 8;  // multiplying waves
 constexpr uint32_t kShareAll = 0x7FFFFFFFu;

@@ -319,6 +319,10 @@ def test_tiled_full_size_70b_layer(dev):
     torch.cuda.empty_cache()
 
 
+def _cus(dev):
+    return torch.cuda.get_device_properties(dev).multi_processor_count
+
+
 def _rare_symbols(dtype, chunks):
     """Bytes whose table is nearly one symbol, with chunks of nothing but rare
     ones: 12 bits a symbol there, the most words a step can take."""
@@ -331,12 +335,12 @@ def _rare_symbols(dtype, chunks):
 
 @pytest.mark.parametrize("tile", [None, (4, 0), (4, 1)])
 @pytest.mark.parametrize("dtype", ["bf16", "u8", "u4"])
-@pytest.mark.parametrize("chunks", [1, 1024, 1025, 2048, 2049])
-def test_launches_around_the_small_kernels_limits(dev, chunks, dtype, tile):
-    """Up to four, up to eight and more 64-lane chunks to a compute unit (256 on
-    an MI355X): whole and ragged chunks of 1 KiB, byte runs and both tile orders,
+@pytest.mark.parametrize("per_cu,more", [(0, 1), (4, 0), (4, 1), (8, 0), (8, 1)])
+def test_launches_around_the_small_kernels_limits(dev, per_cu, more, dtype, tile):
+    """Up to four, up to eight and more 64-lane chunks to a compute unit: whole and ragged chunks of 1 KiB, byte runs and both tile orders,
     every symbol width.  4-bit chunks have 32 steps and run on a kernel for each of
     the three; bf16 and 8-bit ones (8 and 16 steps) all on the general kernel."""
+    chunks = per_cu * _cus(dev) + more
     say("small kernel", chunks, dtype, tile)
     d = _rare_symbols(dtype, chunks)
     if tile is None:
@@ -349,10 +353,6 @@ def test_launches_around_the_small_kernels_limits(dev, chunks, dtype, tile):
     blob = wc.encode(entries, chunk_bytes=1024, **kw)
     assert blob.n_chunks == chunks
     check_exact([(dtype, d)], blob, gpu_decode(blob, dev))
-
-
-def _cus(dev):
-    return torch.cuda.get_device_properties(dev).multi_processor_count
 
 
 def _launch_kernel(chunks, dtype, cb, cus):

@@ -73,11 +73,19 @@ def _case(rng):
                          tile_order=order)
 
 
-def test_random_blobs_decode_like_the_oracle(dev):
+@pytest.mark.parametrize("more", [False, True])
+def test_random_blobs_decode_like_the_oracle(dev, more):
+    """more: those of 64 lanes and chunks of up to 4 KiB again, in a launch of more than
+    eight chunks to a compute unit, which takes them to the general kernel."""
     rng = np.random.default_rng(260615789)
     err = torch.zeros(1, dtype=torch.int32, device=dev)
+    chunks = 8 * torch.cuda.get_device_properties(dev).multi_processor_count + 1
     for i in range(120):
         entries, kw = _case(rng)
+        if more:
+            if kw["lanes"] != 64 or kw["chunk_bytes"] > 4096:
+                continue
+            entries.append(("u8", np.full(chunks * kw["chunk_bytes"], i, np.uint8)))
         say(f"random blob {i}: {[(e[0], np.asarray(e[1]).nbytes) for e in entries]} {kw}")
         blob = wc.encode(entries, threads=2, **kw)
         ref = oracle.decode(blob.tobytes())
