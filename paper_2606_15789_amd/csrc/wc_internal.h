@@ -122,10 +122,10 @@ struct BlobPriv {
 // every word): two launches of 1792 chunks together / one alone, general and small,
 // 64 KiB int8 chunks 117 and 150 / 97 and 83 us, bf16 80 and 88 / 62 and 48, int4 215
 // and 224 / 181 and 123; of 1340, 116 and 119 / 97 and 82, 75 and 71 / 61 and 47,
-// 214 and 176 / 180 and 122.  It is kept while a launch alone gains more than two
-// lose: int8, with the most words to a step, up to 5.5 chunks to a compute unit, and
-// so 16-bit chunks of fewer than kLongSteps steps (1700 of 16 KiB: 36 and 43 / 27 and
-// 23 us), the others up to 8.
+// 214 and 176 / 180 and 122; of 2040, bf16 79 and 94 / 61 and 49, int4 216 and 243 / 181
+// and 124.  It ends about where two lose what a launch alone gains: int8, with the most
+// words to a step, at 5.5 chunks to a compute unit, and so 16-bit chunks of fewer than
+// kLongSteps steps (1700 of 16 KiB: 36 and 43 / 27 and 23 us), the others at 8.
 //
 // Column-block tiles of 64 rows and more are written 16 bytes a row at a time, which
 // bounds any kernel (0.34 TB/s): up to four chunks to a compute unit the small one is
